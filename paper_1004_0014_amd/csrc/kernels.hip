@@ -72,6 +72,8 @@ __device__ __forceinline__ float clampv(float x, float lo, float hi) { return fm
 // (a fixed DPP tree: the same order on every call, deterministic).
 extern "C" __device__ __attribute__((const)) double __ockl_wfred_add_f64(double);
 __device__ __forceinline__ double wave_sum(double v) { return __ockl_wfred_add_f64(v); }
+extern "C" __device__ __attribute__((const)) float __ockl_wfred_min_f32(float);
+__device__ __forceinline__ float wave_min(float v) { return __ockl_wfred_min_f32(v); }
 
 // Block (256 threads = 4 waves) sum of NM doubles per thread; thread t < nm
 // writes dst[t * stride].  Only waves 0 .. nw-1 hold data (the others add
@@ -902,24 +904,32 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
 
 // ------------------------------------------ FP32 ray march, LDS-staged ----
 // The same march as k_march_f32 (same rays per wave, same segments, same
-// sample positions, weights and summation order: bitwise the same sums), but
-// each wave gathers its taps from a private LDS copy of the cells it is about
-// to sample instead of through the vector L1.  The wave's sample range is cut
-// into chunks of S sample indices; for each chunk the wave finds the index
-// box of the cells its active lanes will read (the floor cells of the first
-// and last sample of each lane's share of the chunk, plus one: positions are
-// monotone in n, so the extremes bound every sample between), copies that
-// box from the image into LDS with coalesced row loads (one 16-byte lane
-// load per cell at C = 4), and marches the chunk out of LDS.  A chunk whose
-// box exceeds the wave's buffer is retried at half the length; at the
-// shortest length it falls back to gathering through the L1.  A short box
-// grows the next chunk.  Each staged cell serves ~40 sample taps at paper
-// scale, so the L1 sees a few coalesced row loads per chunk instead of 8
-// scattered cells per sample.
-// LDS per wave: six 256-thread blocks per CU at C <= 4 (74 VGPRs), five at
-// C = 6 (85-94 VGPRs), four at C = 8 (114 VGPRs), the most that the
-// registers allow in each case (at C = 6, 6 KB and five blocks beat 9 KB
-// and four by 5-9 % at paper scale)
+// sample positions), but each wave gathers its taps from a private LDS copy of
+// the cells it is about to sample instead of through the vector L1.  The
+// wave's sample range is cut into chunks of S sample indices; for each chunk
+// the wave finds the index box of the cells its rays can read (from the
+// extremes of the rays' coefficients, see below), copies that box from the
+// image to LDS with loads that go there directly, whole rows along the
+// fastest axis, and marches the chunk out of LDS.  A chunk whose box exceeds
+// the wave's buffer is retried at half the length; at the shortest length it
+// falls back to gathering through the L1.  A short box grows the next chunk.
+// Each staged cell serves ~40 sample taps at paper scale, so the L1 sees a few
+// coalesced row loads per chunk instead of 8 scattered cells per sample.
+//
+// What bounds it: VALU issue first (1.16 wave-instructions per CU and clock
+// here; independent FMAs alone reach 1.48), then the LDS reads (0.56 of the
+// clocks).  Hence the chunk set-up without wave reductions or divisions (the
+// box cost six reductions a chunk and the copy 19 instructions per 64 cells),
+// no clamps where the box lies inside the image, and no registers or waits in
+// the copy.  Measured (march alone, before -> now): K = 3 at 256x256x100,
+// 512x384 pixels, 57 deg: 160.5 -> 144 us; one channel there: 163 -> 140 us;
+// K = 4 at 256x256x128: 205 -> 172 us; K = 5 at 512x512x160, 1024x768 pixels:
+// 1531 -> 1227 us.  Most of the gain at K = 4 and 5 is the staging of 24-byte
+// cells as planes of 16 and 4 bytes: three 8-byte reads a cell pair kept the
+// LDS busy 0.77 of the clocks, 16 + 4 byte reads 0.55.
+// LDS per wave: six 256-thread blocks per CU at C <= 4 (72 VGPRs), five at
+// C = 6 (83-94 VGPRs), four at C = 8 (108 VGPRs), the most that the
+// registers allow in each case.
 template <int C>
 constexpr int stage_bytes() { return C <= 6 ? 6144 : 9216; }
 template <int C>
@@ -943,47 +953,63 @@ __device__ __forceinline__ int small_quot(int x, float rd)
     return (int)(((float)x + 0.5f) * rd);
 }
 
-// The cells at byte offset `off` of a staging buffer of C-float cells and
-// the cell after it.
-template <int C>
-__device__ __forceinline__ void lds_pair(const char* st, unsigned off, float (&a)[C], float (&b)[C])
+// A wave's staging buffer: the KC used channels of C-channel cells in planes
+// that a load to LDS can fill, n16 planes of 16-byte quadruples of channels,
+// then n4 planes of single channels (the fifth and sixth channel of 24-byte
+// cells, which the LDS serves faster as 16 + 4 bytes than as three 8-byte
+// pieces; all of a cell of one or two channels).  `buf` cells fit.
+template <int C, int KC>
+struct Stage {
+    static constexpr int n16 = C / 4, n4 = C % 4 ? KC - 4 * n16 : 0;
+    static constexpr int bytes = stage_bytes<C>(), buf = bytes / (16 * n16 + 4 * n4) & ~3;
+    static constexpr int single = 16 * n16 * buf;   // where the single-channel planes start
+    // a cell index is kept in bytes of the planes that are read most simply
+    static constexpr int unit = n4 ? 4 : 16;
+};
+
+// The cells x and x + 1 at the position `loc` (unit bytes a cell, from the
+// start of the first plane of that unit) of the staging buffer at byte `own`
+// of the block's LDS.
+template <int C, int KC>
+__device__ __forceinline__ void lds_pair(const char* st, unsigned own, unsigned loc, CellPair<C>& P)
 {
-    if constexpr (C % 4 == 0) {
-        const float4* q = (const float4*)(st + off);
+    using G = Stage<C, KC>;
 #pragma unroll
-        for (int h = 0; h < C / 4; ++h) {
-            const float4 u = q[h], v = q[C / 4 + h];
-            a[4 * h] = u.x; a[4 * h + 1] = u.y; a[4 * h + 2] = u.z; a[4 * h + 3] = u.w;
-            b[4 * h] = v.x; b[4 * h + 1] = v.y; b[4 * h + 2] = v.z; b[4 * h + 3] = v.w;
-        }
-    } else if constexpr (C % 2 == 0) {
-        // 8-byte aligned cells (C = 2, 6): pairs of channels
+    for (int h = 0; h < G::n16; ++h) {
+        // (loc holds `own` already, in the unit of the single-channel planes
+        // together with their offset)
+        const unsigned at = G::unit == 16 ? loc : (loc << 2) + (own - 4u * (own + G::single));
+        const float4* q = (const float4*)(st + at + h * 16 * G::buf);
+        const float4 u = q[0], v = q[1];
+        P.a[4 * h] = u.x; P.a[4 * h + 1] = u.y; P.a[4 * h + 2] = u.z; P.a[4 * h + 3] = u.w;
+        P.b[4 * h] = v.x; P.b[4 * h + 1] = v.y; P.b[4 * h + 2] = v.z; P.b[4 * h + 3] = v.w;
+    }
 #pragma unroll
-        for (int h = 0; h < C / 2; ++h) {
-            const float2 u = *(const float2*)(st + off + 8 * h), v = *(const float2*)(st + off + 4 * C + 8 * h);
-            a[2 * h] = u.x; a[2 * h + 1] = u.y; b[2 * h] = v.x; b[2 * h + 1] = v.y;
-        }
-    } else {
-        const float* q = (const float*)(st + off);
-        a[0] = q[0];
-        b[0] = q[1];
+    for (int j = 0; j < G::n4; ++j) {
+        const float* q = (const float*)(st + loc + 4 * G::buf * j);
+        P.a[4 * G::n16 + j] = q[0];
+        P.b[4 * G::n16 + j] = q[1];
     }
 }
 
-// Copies one C-float cell (global, 4C-byte aligned) into a staging buffer.
-template <int C>
-__device__ __forceinline__ void stage_cell(const char* src, float* dst)
+// A wave-uniform integer moved to a scalar register (opaque, or the compiler
+// moves the conversion behind it and the arithmetic stays on the VALU).
+__device__ __forceinline__ int scalar(int v)
 {
-    if constexpr (C % 4 == 0) {
-#pragma unroll
-        for (int h = 0; h < C / 4; ++h) ((float4*)dst)[h] = ((const float4*)src)[h];
-    } else if constexpr (C % 2 == 0) {
-#pragma unroll
-        for (int h = 0; h < C / 2; ++h) ((float2*)dst)[h] = ((const float2*)src)[h];
-    } else {
-        static_assert(C == 1, "cells of 1, 2, 4, 6 or 8 channels");
-        *dst = *(const float*)src;
-    }
+    asm("" : "+v"(v));
+    return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Copies `B` bytes (4 or 16) a lane from each lane's `src` to the LDS at the
+// wave-uniform dst + B x lane, asynchronously (counted by vmcnt).
+template <int B>
+__device__ __forceinline__ void load_to_lds(const char* src, float* dst)
+{
+    typedef const __attribute__((address_space(1))) void* G;
+    typedef __attribute__((address_space(3))) void* L;
+    static_assert(B == 4 || B == 16, "sizes of a load to LDS");
+    if constexpr (B == 4) __builtin_amdgcn_global_load_lds((G)src, (L)dst, 4, 0, 0);
+    else __builtin_amdgcn_global_load_lds((G)src, (L)dst, 16, 0, 0);
 }
 
 // KC: the channels whose sums are used (A.kc: the moments and the projection
@@ -996,7 +1022,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
     static_assert(KC >= 1 && KC <= C, "used channels");
     constexpr int CB = 4 * C;                    // bytes per cell
     constexpr int kStageBytes = stage_bytes<C>();
-    constexpr int BUF = kStageBytes / CB;        // cells per wave
+    using G = Stage<C, KC>;
+    constexpr int BUF = G::buf;                  // cells per wave
     const RayGeom& g = A.g;
     const int rpb = 256 / A.ms.seg;
     const int rloc = threadIdx.x % rpb, sid = threadIdx.x / rpb;
@@ -1055,22 +1082,50 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
                     dqz = (float)(g.dt * rr.dq[2]);
         const int YS = A.ys, ZS = A.zs, YZ = A.ys + A.zs, PY = A.py;
         const char* vb = (const char*)A.vol;
+        // The extremes over the wave's rays of a position's two coefficients
+        // bound all its positions: every ray starts at the source, so per
+        // axis the ray with the smallest step also has the smallest offset at
+        // na, and fma is monotone in each operand, rounding included (f >= 0).
+        // Lane 0..2 (axis x, y, z) holds the lower bound's (offset, step),
+        // lane 3..5 the negated upper bound's, so one minimum serves both.
+        const bool any = rr.n1 >= rr.n0;
+        float bq, bd, bn;
+        {
+            const float big = 3.0e38f;
+            const float e[6] = {q0x, q0y, q0z, -q0x, -q0y, -q0z}, d[6] = {dqx, dqy, dqz, -dqx, -dqy, -dqz};
+            bq = bd = 0.f;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const float mq = wave_min(any ? e[i] : big), md = wave_min(any ? d[i] : big);
+                bq = lane == i ? mq : bq;
+                bd = lane == i ? md : bd;
+            }
+            const int ax = lane >= 3 ? lane - 3 : lane;
+            bn = ax == 0 ? A.fn1[0] : (ax == 1 ? A.fn1[1] : A.fn1[2]);
+        }
         // the chunk's samples: the same positions, weights and order as
         // in k_march_f32; a lane reloads its cells P (the pairs at +0, +y,
         // +z, +y+z) only when they change
-        // (fm: the sample's index relative to na, as a float)
-        auto step = [&](float fm, CellPair<C> (&P)[4], auto&& load) {
-            float qx = __builtin_amdgcn_fmed3f(fmaf(fm, dqx, q0x), 0.f, A.fn1[0]);
-            float qy = __builtin_amdgcn_fmed3f(fmaf(fm, dqy, q0y), 0.f, A.fn1[1]);
-            float qz = __builtin_amdgcn_fmed3f(fmaf(fm, dqz, q0z), 0.f, A.fn1[2]);
+        // (fm: the sample's index relative to na, as a float; clamp: positions
+        // may lie outside the support and are clamped to it -- wave-uniform)
+        auto step = [&](bool clamp, float fm, CellPair<C> (&P)[4], auto&& load) {
+            float qx = fmaf(fm, dqx, q0x), qy = fmaf(fm, dqy, q0y), qz = fmaf(fm, dqz, q0z);
+            if (clamp) {
+                // (opaque, or the branch would become clamps and selects)
+                asm volatile("" : "+v"(qx), "+v"(qy), "+v"(qz));
+                qx = __builtin_amdgcn_fmed3f(qx, 0.f, A.fn1[0]);
+                qy = __builtin_amdgcn_fmed3f(qy, 0.f, A.fn1[1]);
+                qz = __builtin_amdgcn_fmed3f(qz, 0.f, A.fn1[2]);
+            }
             const int ix = (int)qx, iy = (int)qy, iz = (int)qz;
             const float ax = __builtin_amdgcn_fractf(qx), ay = __builtin_amdgcn_fractf(qy),
                         az = __builtin_amdgcn_fractf(qz);
             load(ix, iy, iz);
-            const float bx = 1.f - ax, by = 1.f - ay, bz = 1.f - az;
-            const float w00 = by * bz, w10 = ay * bz, w01 = by * az, w11 = ay * az;
-            const float w000 = bx * w00, w100 = ax * w00, w010 = bx * w10, w110 = ax * w10;
-            const float w001 = bx * w01, w101 = ax * w01, w011 = bx * w11, w111 = ax * w11;
+            // each pair of weights from one product and one difference
+            const float bz = 1.f - az;
+            const float w10 = ay * bz, w00 = bz - w10, w11 = ay * az, w01 = az - w11;
+            const float w100 = ax * w00, w000 = w00 - w100, w110 = ax * w10, w010 = w10 - w110;
+            const float w101 = ax * w01, w001 = w01 - w101, w111 = ax * w11, w011 = w11 - w111;
 #pragma unroll
             for (int c = 0; c < KC; ++c) {
                 float t = acc[c];
@@ -1092,46 +1147,30 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
             // the chunk [c0, c1) and the box of the cells its samples read;
             // a box beyond the buffer is retried at half the length (in a
             // loop of its own, so the chunk loop has a single way round)
-            int c1, lo0, lo1, lo2, hi0, hi1, hi2, dx, dy, dz, dxy, cells;
+            int c1, lo0, lo1, lo2, dx, dy, dz, dxy, cells;
+            bool inside;   // no position of the chunk needs the clamp
             for (;;) {
                 c1 = min(nb, c0 + S);
-                // this lane's samples in the chunk, and the cells they read
-                const int s0 = max(c0, rr.n0), s1 = min(c1 - 1, rr.n1);
-                lo0 = lo1 = lo2 = INT_MAX;
-                hi0 = hi1 = hi2 = INT_MIN;
-                if (s0 <= s1) {
-                    const float fa = (float)(s0 - na), fb = (float)(s1 - na);
-                    const float xa = __builtin_amdgcn_fmed3f(fmaf(fa, dqx, q0x), 0.f, A.fn1[0]);
-                    const float ya = __builtin_amdgcn_fmed3f(fmaf(fa, dqy, q0y), 0.f, A.fn1[1]);
-                    const float za = __builtin_amdgcn_fmed3f(fmaf(fa, dqz, q0z), 0.f, A.fn1[2]);
-                    const float xb = __builtin_amdgcn_fmed3f(fmaf(fb, dqx, q0x), 0.f, A.fn1[0]);
-                    const float yb = __builtin_amdgcn_fmed3f(fmaf(fb, dqy, q0y), 0.f, A.fn1[1]);
-                    const float zb = __builtin_amdgcn_fmed3f(fmaf(fb, dqz, q0z), 0.f, A.fn1[2]);
-                    lo0 = (int)fminf(xa, xb);
-                    lo1 = (int)fminf(ya, yb);
-                    lo2 = (int)fminf(za, zb);
-                    hi0 = (int)fmaxf(xa, xb) + 1;
-                    hi1 = (int)fmaxf(ya, yb) + 1;
-                    hi2 = (int)fmaxf(za, zb) + 1;
-                }
-                lo0 = __ockl_wfred_min_i32(lo0);
-                lo1 = __ockl_wfred_min_i32(lo1);
-                lo2 = __ockl_wfred_min_i32(lo2);
-                hi0 = __ockl_wfred_max_i32(hi0);
-                hi1 = __ockl_wfred_max_i32(hi1);
-                hi2 = __ockl_wfred_max_i32(hi2);
-                if (lo0 > hi0) break;   // no lane samples this chunk
-                dx = hi0 - lo0 + 1;
-                dy = hi1 - lo1 + 1;
-                dz = hi2 - lo2 + 1;
+                const float fa = (float)(c0 - na), fb = (float)(c1 - 1 - na);
+                float v = fminf(fmaf(fa, bd, bq), fmaf(fb, bd, bq));
+                v = lane >= 3 ? -v : v;
+                const float vc = __builtin_amdgcn_fmed3f(v, 0.f, bn);
+                inside = (__ballot(v == vc) & 63u) == 63u;
+                const int iv = (int)vc;
+                lo0 = __builtin_amdgcn_readlane(iv, 0);
+                lo1 = __builtin_amdgcn_readlane(iv, 1);
+                lo2 = __builtin_amdgcn_readlane(iv, 2);
+                dx = __builtin_amdgcn_readlane(iv, 3) - lo0 + 2;
+                dy = __builtin_amdgcn_readlane(iv, 4) - lo1 + 2;
+                dz = __builtin_amdgcn_readlane(iv, 5) - lo2 + 2;
                 dxy = dx * dy;
                 cells = dxy * dz;
-                if (cells <= BUF || S <= 4) break;
+                // (each extent on its own first: the products may overflow)
+                const bool fits = dx <= BUF && dy <= BUF && dz <= BUF && dxy <= BUF && cells <= BUF;
+                if (fits) break;
+                cells = BUF + 1;
+                if (S <= 4) break;
                 S >>= 1;
-            }
-            if (lo0 > hi0) {
-                c0 = c1;
-                continue;
             }
             if (cells > BUF) {
                 // the rays spread too far for the buffer even over 4 samples
@@ -1139,39 +1178,65 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
                 gather = true;
                 break;
             }
+            // this lane's samples in the chunk
+            const int s_lo = max(c0, rr.n0), s_hi = min(c1 - 1, rr.n1);
+            const unsigned long long some = __ballot(s_lo <= s_hi);
+            if (some == 0) {   // no lane samples this chunk
+                c0 = c1;
+                continue;
+            }
             {
                 // every lane is past the previous chunk's reads (the wave runs
                 // in order); copy the box, rows along the fastest axis
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_wave_barrier();
-                // cell e = row dx + lx, row = lz dy + ly: each lane starts at
-                // e = lane and advances by 64 cells, i.e. by sz slices, sy
-                // rows and sx cells with at most one carry into the row and
-                // one into the slice; its image offset follows the same
-                // carries (unsigned: the offset one step past the box may
-                // wrap, but every offset loaded is that of a box cell)
+                // a pass copies rpp whole rows (64 / dx; a longer row takes
+                // its passes 64 cells at a time): lane = (row r of the pass,
+                // cell lx of the row) and only the row advances, by sz
+                // slices and sy rows with at most one carry, so a pass costs
+                // half the index arithmetic of 64 consecutive cells
                 const float rdx = __builtin_amdgcn_rcpf((float)dx), rdy = __builtin_amdgcn_rcpf((float)dy);
-                const int row = small_quot(lane, rdx);
-                int lx = lane - row * dx;
-                const int lz = small_quot(row, rdy);
-                int ly = row - lz * dy;
-                const int srow = __builtin_amdgcn_readfirstlane(small_quot(64, rdx));
-                const int sz = __builtin_amdgcn_readfirstlane(small_quot(srow, rdy));
-                const int sx = 64 - srow * dx, sy = srow - sz * dy;
+                const bool wide = dx > 64;
+                const int rpp = wide ? 1 : scalar(small_quot(64, rdx));
+                const int r0 = wide ? 0 : small_quot(lane, rdx);
+                const int rows = dy * dz;
+                const int sz = scalar(small_quot(rpp, rdy));
+                const int sy = rpp - sz * dy;
                 const unsigned uYS = (unsigned)YS, uZS = (unsigned)ZS;
-                const unsigned a0 = (unsigned)(sx * CB) + (unsigned)sy * uYS + (unsigned)sz * uZS;
-                const unsigned a1 = uYS - (unsigned)(dx * CB), a2 = uZS - (unsigned)dy * uYS;
-                unsigned goff = (unsigned)((lo0 + lx) * CB) + __umul24(__umul24(lo2 + lz, PY) + lo1 + ly, YS);
-                for (int e = lane; e < cells; e += 64) {
-                    stage_cell<C>(vb + goff, st + e * C);
-                    lx += sx;
-                    const bool carry_x = lx >= dx;
-                    lx -= carry_x ? dx : 0;
-                    ly += sy + (carry_x ? 1 : 0);
-                    const bool carry_y = ly >= dy;
-                    ly -= carry_y ? dy : 0;
-                    goff += a0 + (carry_x ? a1 : 0u) + (carry_y ? a2 : 0u);
+                const unsigned a0 = (unsigned)sy * uYS + (unsigned)sz * uZS, a1 = a0 + uZS - (unsigned)dy * uYS;
+                const int zr = small_quot(r0, rdy);
+                for (int x0 = 0; x0 < dx; x0 += 64) {
+                    const int lx = lane - (int)__umul24(r0, dx) + x0;
+                    // rows left for this lane (none: its cell is beyond the row
+                    // or belongs to the next pass)
+                    const int left = (r0 < rpp && lx < dx) ? rows - r0 : 0;
+                    int ly = r0 - (int)__umul24(zr, dy);
+                    unsigned goff = (unsigned)((lo0 + lx) * CB) + __umul24(__umul24(lo2 + zr, PY) + lo1 + ly, YS);
+                    auto next = [&] {
+                        ly += sy;
+                        const bool carry = ly >= dy;
+                        ly -= carry ? dy : 0;
+                        goff += carry ? a1 : a0;
+                    };
+                    // straight to LDS, without registers and without a wait
+                    // before the last pass is issued; the lanes' cells are
+                    // consecutive: r0 dx + lx = lane + x0 cells into the pass
+                    int cell = x0;
+                    for (int p = 0; p < rows; p += rpp) {
+                        if (left > p) {
+                            const char* src = vb + goff;
+#pragma unroll
+                            for (int h = 0; h < G::n16; ++h)
+                                load_to_lds<16>(src + 16 * h, st + 4 * (cell + h * BUF));
+#pragma unroll
+                            for (int j = 0; j < G::n4; ++j)
+                                load_to_lds<4>(src + 16 * G::n16 + 4 * j, st + G::single / 4 + cell + j * BUF);
+                        }
+                        next();
+                        cell += rpp * dx;
+                    }
                 }
+                __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the loads to LDS are done
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -1184,29 +1249,30 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
             // arithmetic: the wrap of the products cancels in the difference)
             CellPair<C> P[4];
             unsigned last = ~0u;
-            const int s_lo = max(c0, rr.n0), s_hi = min(c1 - 1, rr.n1);
-            const unsigned cy = (unsigned)(dx * CB), cz = (unsigned)(dxy * CB);
+            const unsigned cy = (unsigned)(dx * G::unit), cz = (unsigned)(dxy * G::unit);
             // (offsets from the start of the block's LDS: the wave's buffer
             // starts kStageBytes x wave into it)
-            const unsigned base = (unsigned)lo2 * cz + (unsigned)lo1 * cy + (unsigned)(lo0 * CB) -
-                                  (unsigned)__builtin_amdgcn_readfirstlane(wave * kStageBytes);
+            const unsigned own = (unsigned)__builtin_amdgcn_readfirstlane(wave * kStageBytes);
+            unsigned base = own + (G::unit == 16 ? 0u : (unsigned)G::single) -
+                            ((unsigned)lo2 * cz + (unsigned)lo1 * cy + (unsigned)(lo0 * G::unit));
+            asm("" : "+s"(base));   // one sum, not regrouped by axis in the loop
             const char* stb = smem;
+            auto from_lds = [&](int ix, int iy, int iz) {
+                const unsigned loc = mad_u24(iz, cz, mad_u24(iy, cy, (unsigned)(ix * G::unit) + base));
+                if (loc != last) {
+                    last = loc;
+                    lds_pair<C, KC>(stb, own, loc, P[0]);
+                    lds_pair<C, KC>(stb, own, loc + cy, P[1]);
+                    lds_pair<C, KC>(stb, own, loc + cz, P[2]);
+                    lds_pair<C, KC>(stb, own, loc + cz + cy, P[3]);
+                }
+            };
             // the samples, counted once per chunk; the loop runs on the
             // index as a float (0 <= n - na < 2^24: exact)
             const int cnt = s_hi - s_lo + 1;
             if (cnt > 0) nsamp += cnt;
             const float fe = (float)(s_hi - na);
-            for (float fm = (float)(s_lo - na); fm <= fe; fm += 1.0f)
-                step(fm, P, [&](int ix, int iy, int iz) {
-                    const unsigned loc = mad_u24(iz, cz, mad_u24(iy, cy, (unsigned)(ix * CB) - base));
-                    if (loc != last) {
-                        last = loc;
-                        lds_pair<C>(stb, loc, P[0].a, P[0].b);
-                        lds_pair<C>(stb, loc + cy, P[1].a, P[1].b);
-                        lds_pair<C>(stb, loc + cz, P[2].a, P[2].b);
-                        lds_pair<C>(stb, loc + cz + cy, P[3].a, P[3].b);
-                    }
-                });
+            for (float fm = (float)(s_lo - na); fm <= fe; fm += 1.0f) step(!inside, fm, P, from_lds);
             if (cells * 3 < BUF && S < 64) S <<= 1;
             c0 = c1;
         }
@@ -1217,7 +1283,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
             if (g1 >= g0) nsamp += g1 - g0 + 1;
             const float fe = (float)(g1 - na);
             for (float fm = (float)(g0 - na); fm <= fe; fm += 1.0f)
-                step(fm, P, [&](int ix, int iy, int iz) {
+                step(true, fm, P, [&](int ix, int iy, int iz) {
                     const int voff = ix * CB + (int)__umul24(__umul24(iz, PY) + iy, YS);
                     if (voff != last) {
                         last = voff;
