@@ -667,6 +667,28 @@ __global__ void __launch_bounds__(256) k_march(RayGeom g, MarchShape ms, int til
 // gives each XCD one contiguous band of detector rows, so that the rays
 // sharing an XCD's L2 cross the same part of the volume.)
 
+// The march's tile (tu, tv) of dispatch index b: within each XCD's band of
+// rows (xcd_tile) the tiles go from the middle column outwards.  The rays
+// through the middle of the volume are the longest, and a block takes about
+// half the launch's time: with the long blocks first the short ones fill in
+// at the end.
+__device__ __forceinline__ void march_tile(int b, int nb, int tiles_u, int& tu, int& tv)
+{
+    const int q = nb >> 3, rem = nb & 7, x = b & 7;
+    const int s = x * q + min(x, rem), n = q + (x < rem ? 1 : 0), i = b >> 3;
+    const int k = n / tiles_u;
+    int t = s + i;
+    if (i < k * tiles_u) {
+        const int r = i / k, c = tiles_u >> 1;
+        int col = (r & 1) ? c - ((r + 1) >> 1) : c + (r >> 1);
+        col -= s % tiles_u;
+        if (col < 0) col += tiles_u;
+        t = s + col + (i - r * k) * tiles_u;
+    }
+    tv = t / tiles_u;
+    tu = t - tv * tiles_u;
+}
+
 // One padded cell pair (x and x+1) of C float channels.
 template <int C>
 struct CellPair {
@@ -1028,8 +1050,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
     const int rpb = 256 / A.ms.seg;
     const int rloc = threadIdx.x % rpb, sid = threadIdx.x / rpb;
     const int rows = rpb / A.ms.tile_u;
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int tu = tile % A.tiles_u, tv = tile / A.tiles_u;
+    int tu, tv;
+    march_tile(blockIdx.x, gridDim.x, A.tiles_u, tu, tv);
     const int iu = tu * A.ms.tile_u + rloc % A.ms.tile_u;
     const int iv = tv * rows + rloc / A.ms.tile_u;
     const bool valid = iu < g.nu && iv < g.nv;
