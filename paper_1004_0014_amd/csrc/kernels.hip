@@ -75,21 +75,71 @@ __device__ __forceinline__ double wave_sum(double v) { return __ockl_wfred_add_f
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_min_f32(float);
 __device__ __forceinline__ float wave_min(float v) { return __ockl_wfred_min_f32(v); }
 
+// Sums over the wave of N doubles per lane (N a multiple of 4), in fewer
+// exchanges than N separate sums: swapping the half waves of two registers
+// and adding leaves one value's sums in each half, swapping the 16-lane rows
+// of two such registers leaves four values in the rows of one; only N / 4
+// registers then take the four steps within a row.  The sum of value
+// i + (N/4) q ends in every lane of row q (lanes 16 q ..) of v[i].  A fixed
+// order: deterministic.
+__device__ __forceinline__ void swap_add(double& a, double b, bool rows)
+{
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    union { double d; unsigned w[2]; } x{a}, y{b};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const u2 r = rows ? __builtin_amdgcn_permlane16_swap(x.w[i], y.w[i], false, false)
+                          : __builtin_amdgcn_permlane32_swap(x.w[i], y.w[i], false, false);
+        x.w[i] = r.x;
+        y.w[i] = r.y;
+    }
+    a = x.d + y.d;
+}
+template <int CTRL>
+__device__ __forceinline__ double row_rot(double v)
+{
+    union { double d; int w[2]; } x{v};
+    x.w[0] = __builtin_amdgcn_update_dpp(0, x.w[0], CTRL, 0xf, 0xf, false);
+    x.w[1] = __builtin_amdgcn_update_dpp(0, x.w[1], CTRL, 0xf, 0xf, false);
+    return x.d;
+}
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N])
+{
+    static_assert(N % 4 == 0, "N in quarters");
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) swap_add(v[i], v[i + N / 2], false);
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) swap_add(v[i], v[i + N / 4], true);
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+        v[i] += row_rot<0x128>(v[i]);   // row_ror:8, 4, 2, 1
+        v[i] += row_rot<0x124>(v[i]);
+        v[i] += row_rot<0x122>(v[i]);
+        v[i] += row_rot<0x121>(v[i]);
+    }
+}
 // Block (256 threads = 4 waves) sum of NM doubles per thread; thread t < nm
 // writes dst[t * stride].  Only waves 0 .. nw-1 hold data (the others add
 // nothing and skip their sums).  Fixed order: wave tree, then waves 0..nw-1.
+// (16 moments: ~100 instructions against ~340 for 16 separate sums, which
+// the block's other waves wait for.)
 template <int NM>
 __device__ __forceinline__ void block_sum_store(double (&m)[NM], int nm, double* dst, int stride,
                                                 int nw = 4)
 {
-    __shared__ double red[4][NM];
+    constexpr int N = (NM + 3) / 4 * 4, Q = N / 4;
+    __shared__ double red[4][N];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (wv < nw) {
+        double v[N];
 #pragma unroll
-        for (int i = 0; i < NM; ++i) {
-            double s = wave_sum(m[i]);
-            if (lane == 0) red[wv][i] = s;
-        }
+        for (int i = 0; i < N; ++i) v[i] = i < NM ? m[i] : 0.0;
+        wave_sums(v);
+        double s = v[0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) s = (lane & 15) == i ? v[i] : s;
+        if ((lane & 15) < Q) red[wv][(lane >> 4) * Q + (lane & 15)] = s;
     }
     __syncthreads();
     if ((int)threadIdx.x < nm) {
@@ -426,29 +476,23 @@ struct RaySeg {
 // One direction of the slab tests along a ray: the coordinate o + t d,
 // with 1 / d and the offsets that fold the dilation into one FMA per bound:
 // t = lo * inv + nlo is where the coordinate reaches lo - h, t = hi * inv + nhi
-// where it reaches hi + h.  |d| < 1e-20: the coordinate is taken as
-// constant (it moves by < 1e-16 index units over any ray; 1 / d would
-// overflow the offsets).
+// where it reaches hi + h.  1 / d is the hardware reciprocal (1 ulp, far
+// inside the half-cell slack of the dilation).  |d| < 1e-20 is taken as 1e-20
+// (the coordinate moves by < 1e-16 index units over any ray): both bounds are
+// then beyond the ray, on opposite sides if the coordinate lies between them.
 struct SlabAxis {
-    float o, inv, nlo, nhi;
-    bool flat;
-    __device__ __forceinline__ void init(float o_, float d, float h)
+    float inv, nlo, nhi;
+    __device__ __forceinline__ void init(float o, float d, float h)
     {
-        o = o_;
-        flat = fabsf(d) < 1e-20f;
-        inv = flat ? 0.0f : 1.0f / d;
+        inv = __builtin_amdgcn_rcpf(copysignf(fmaxf(fabsf(d), 1e-20f), d));
         nlo = -(o + h) * inv;
         nhi = (h - o) * inv;
     }
-    __device__ __forceinline__ void clip(float lo, float hi, float h, float& ta, float& tb) const
+    __device__ __forceinline__ void clip(float lo, float hi, float& ta, float& tb) const
     {
-        if (!flat) {
-            const float t1 = fmaf(lo, inv, nlo), t2 = fmaf(hi, inv, nhi);
-            ta = fmaxf(ta, fminf(t1, t2));
-            tb = fminf(tb, fmaxf(t1, t2));
-        } else if (!(o >= lo - h && o <= hi + h)) {
-            ta = INFINITY;
-        }
+        const float t1 = fmaf(lo, inv, nlo), t2 = fmaf(hi, inv, nhi);
+        ta = fmaxf(ta, fminf(t1, t2));
+        tb = fminf(tb, fmaxf(t1, t2));
     }
 };
 
@@ -461,12 +505,13 @@ struct SlabAxis {
 __device__ __forceinline__ void refine_by_slabs(const RayGeom& g, const double dq[3], double& tmin,
                                                 double& tmax)
 {
-    const double za = g.qs[2] + tmin * dq[2], zb = g.qs[2] + tmax * dq[2];
+    const double za = fma(tmin, dq[2], g.qs[2]), zb = fma(tmax, dq[2], g.qs[2]);
     // slab s (slices sT .. sT + T - 1) reaches k in [sT - h, sT + T - 1 + h]
+    // (one slab more at each end covers the rounding of 1 / T)
     const float zlo = (float)fmin(za, zb) - g.h[2], zhi = (float)fmax(za, zb) + g.h[2];
-    const float T = (float)g.slab_t, lim = (float)g.nslab + 2.0f;
-    const int s0 = max(0, (int)floorf(fminf(fmaxf((zlo + 1.0f) / T - 1.0f, -2.0f), lim)) - 1);
-    const int s1 = min(g.nslab - 1, (int)floorf(fminf(fmaxf(zhi / T, -2.0f), lim)));
+    const float rT = __builtin_amdgcn_rcpf((float)g.slab_t), lim = (float)g.nslab + 2.0f;
+    const int s0 = max(0, (int)floorf(fminf(fmaxf((zlo + 1.0f) * rT - 1.0f, -2.0f), lim)) - 1);
+    const int s1 = min(g.nslab - 1, (int)floorf(fminf(fmaxf(fmaf(zhi, rT, 1e-3f), -2.0f), lim)));
     const float o0 = (float)g.qs[0], o1 = (float)g.qs[1], d0 = (float)dq[0], d1 = (float)dq[1];
     const float hd = g.h[0] + g.h[1];
     SlabAxis ax, ay, ap, am, az;
@@ -476,22 +521,39 @@ __device__ __forceinline__ void refine_by_slabs(const RayGeom& g, const double d
     am.init(o0 - o1, d0 - d1, hd);
     az.init((float)g.qs[2], (float)dq[2], g.h[2]);
     float tin = INFINITY, tout = -INFINITY;
+    // (no branch in the loop, so that the loads of two slabs are in flight)
+#pragma unroll 2
     for (int s = s0; s <= s1; ++s) {
         const float* b = g.slabs + 10 * s;
-        if (b[8] > b[9]) continue;   // no nonzero voxel in this slab
         float ta = -INFINITY, tb = INFINITY;
-        az.clip(b[8], b[9], g.h[2], ta, tb);
-        ax.clip(b[0], b[1], g.h[0], ta, tb);
-        ay.clip(b[2], b[3], g.h[1], ta, tb);
-        ap.clip(b[4], b[5], hd, ta, tb);
-        am.clip(b[6], b[7], hd, ta, tb);
-        if (ta <= tb) {
-            tin = fminf(tin, ta);
-            tout = fmaxf(tout, tb);
-        }
+        az.clip(b[8], b[9], ta, tb);
+        ax.clip(b[0], b[1], ta, tb);
+        ay.clip(b[2], b[3], ta, tb);
+        ap.clip(b[4], b[5], ta, tb);
+        am.clip(b[6], b[7], ta, tb);
+        const bool in = b[8] <= b[9] && ta <= tb;   // b[8] > b[9]: no nonzero voxel
+        tin = in ? fminf(tin, ta) : tin;
+        tout = in ? fmaxf(tout, tb) : tout;
     }
     tmin = fmax(tmin, (double)tin);
     tmax = fmin(tmax, (double)tout);
+}
+
+// 1 / x and 1 / sqrt(x) in FP64 (x normal and far from the ends of the
+// range) from the hardware approximations, good to 2^-24 or better, and two
+// Newton steps, each doubling the correct bits: within an ulp or two, at a
+// third of the instructions of a division.
+__device__ __forceinline__ double rcp64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(r, fma(-x, r, 1.0), r);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ double rsq64(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+    r = fma(0.5 * r, fma(-x * r, r, 1.0), r);
+    return fma(0.5 * r, fma(-x * r, r, 1.0), r);
 }
 
 // Global sample range [n0, n1] of ray (iu, iv) (n1 < n0: none) on the grid
@@ -507,6 +569,9 @@ struct RayRange {
 __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
 {
     RayRange r;
+    r.n0 = 0;
+    r.n1 = -1;
+    r.dq[0] = r.dq[1] = r.dq[2] = 0.0;
     double u = g.u0 + iu * g.du, v = g.v0 + iv * g.dv;
     double D[3], L2 = 0.0;
 #pragma unroll
@@ -515,14 +580,23 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
         double w = D[a] * g.sp[a];
         L2 += w * w;
     }
-    double L = sqrt(L2);
+    if (!(L2 > 0.0)) return r;
+    const double iL = rsq64(L2);
+    // the length and its quotient by dt corrected once more, so that a
+    // sample exactly on the detector is kept or dropped as by sqrt and /
+    double L = L2 * iL;
+    L = fma(0.5 * iL, fma(-L, L, L2), L);
+    double nl = L * g.inv_dt;
+    nl = fma(g.inv_dt, fma(-nl, g.dt, L), nl);
     double tmin = 0.0, tmax = L;
-    bool hit = L > 0.0;
+    bool hit = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        r.dq[a] = hit ? D[a] / L : 0.0;
-        if (r.dq[a] != 0.0) {
-            double t1 = (g.clo[a] - g.qs[a]) / r.dq[a], t2 = (g.chi[a] - g.qs[a]) / r.dq[a];
+        const double d = D[a] * iL;
+        r.dq[a] = d;
+        if (fabs(d) > 1e-280) {
+            const double i = rcp64(d);
+            const double t1 = (g.clo[a] - g.qs[a]) * i, t2 = (g.chi[a] - g.qs[a]) * i;
             tmin = fmax(tmin, fmin(t1, t2));
             tmax = fmin(tmax, fmax(t1, t2));
         } else if (!(g.qs[a] > g.clo[a] && g.qs[a] < g.chi[a])) {
@@ -530,13 +604,10 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
         }
     }
     if (g.slabs && hit && tmin <= tmax) refine_by_slabs(g, r.dq, tmin, tmax);
-    r.n0 = 0;
-    r.n1 = -1;
     if (!hit || !(tmin <= tmax)) return r;
-    long nlast = (long)floor(L / g.dt);
-    long n0 = (long)ceil(tmin / g.dt) - 1, n1 = (long)floor(tmax / g.dt) + 1;
-    if (n0 < 0) n0 = 0;
-    if (n1 > nlast) n1 = nlast;
+    // (L / dt is below 2^31: checked with the geometry)
+    const double n0 = fmax(ceil(tmin * g.inv_dt) - 1.0, 0.0);
+    const double n1 = fmin(floor(tmax * g.inv_dt) + 1.0, floor(nl));
     if (n1 >= n0) {
         r.n0 = (int)n0;
         r.n1 = (int)n1;
@@ -805,13 +876,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
         rr = ray_range(g, iu, iv);
     }
     int N0 = rr.n1 >= rr.n0 ? rr.n0 : INT_MAX, N1 = rr.n1 >= rr.n0 ? rr.n1 : INT_MIN;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        N0 = min(N0, __shfl_xor(N0, o));
-        N1 = max(N1, __shfl_xor(N1, o));
-    }
-    N0 = __builtin_amdgcn_readfirstlane(N0);
-    N1 = __builtin_amdgcn_readfirstlane(N1);
+    N0 = __builtin_amdgcn_readfirstlane(__ockl_wfred_min_i32(N0));
+    N1 = __builtin_amdgcn_readfirstlane(__ockl_wfred_max_i32(N1));
     if (N0 <= N1) {
         const long span = (long)N1 - N0 + 1;
         const int na = __builtin_amdgcn_readfirstlane(N0 + (int)(span * sid / A.ms.seg));
@@ -1084,13 +1150,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
         rr = ray_range(g, iu, iv);
     }
     int N0 = rr.n1 >= rr.n0 ? rr.n0 : INT_MAX, N1 = rr.n1 >= rr.n0 ? rr.n1 : INT_MIN;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        N0 = min(N0, __shfl_xor(N0, o));
-        N1 = max(N1, __shfl_xor(N1, o));
-    }
-    N0 = __builtin_amdgcn_readfirstlane(N0);
-    N1 = __builtin_amdgcn_readfirstlane(N1);
+    N0 = __builtin_amdgcn_readfirstlane(__ockl_wfred_min_i32(N0));
+    N1 = __builtin_amdgcn_readfirstlane(__ockl_wfred_max_i32(N1));
     float* st = (float*)(smem + wave * kStageBytes);
     if (N0 <= N1) {
         const long span = (long)N1 - N0 + 1;
@@ -1964,6 +2025,7 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy)
     r.du = G.du_mm;
     r.dv = G.dv_mm;
     r.dt = G.step_mm;
+    r.inv_dt = 1.0 / G.step_mm;
     r.nu = G.nu;
     r.nv = G.nv;
     return r;

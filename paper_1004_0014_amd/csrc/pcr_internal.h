@@ -64,7 +64,7 @@ struct RayGeom {
                            // contributes)
     double u0, v0;       // detector coordinate (mm) of pixel 0 along e_u, e_v
     double du, dv;       // pixel pitch (mm)
-    double dt;           // sample spacing (mm)
+    double dt, inv_dt;   // sample spacing (mm), 1 / dt
     int nu, nv;
     // Tighter clipping within the box (null: none): per slab of slab_t
     // slices, 10 floats {i lo, hi; j lo, hi; i+j lo, hi; i-j lo, hi; k lo, hi}
