@@ -1556,7 +1556,6 @@ struct BPArgs {
     int nbx, nby;         // bricks per axis
     int nx, ny, nz;
     double a, b, scale;   // r = scale (p - a y - b) when no residual is given
-    double inv_dt;        // 1 / sample spacing
 };
 
 template <typename R>
@@ -1565,31 +1564,50 @@ struct alignas(4 * sizeof(R)) BPVec4 {
 };
 
 template <typename R>
+__device__ __forceinline__ R fract_of(R x);
+template <> __device__ __forceinline__ float fract_of<float>(float x) { return __builtin_amdgcn_fractf(x); }
+template <> __device__ __forceinline__ double fract_of<double>(double x) { return __builtin_amdgcn_fract(x); }
+// x clamped to [0, 1] (x <= 1 where it is used)
+__device__ __forceinline__ float saturate(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 1.f); }
+__device__ __forceinline__ double saturate(double x) { return fmax(x, 0.0); }
+
+// What bounds the column gather is the latency of a sample's round trip to
+// its LDS run (position, read, add, write: the next sample may touch the same
+// voxels), then VALU issue, so blocks in flight count: 11 words a staged ray
+// and 20 slots a run make 31 KB a block, five to a CU (four with the 16 words
+// and 21 slots of before), and the loop is 16 VALU instructions a sample and
+// column (22 before; alone worth 2 %).  256x256x100 voxels, 512x384 pixels,
+// at 0 / 30 / 90 deg: 907 / 694 / 887 -> 759 / 580 / 725 us.  Tiles of 4 x 32
+// rays (six blocks) 752 / 630 / 710 us; 8 x 4 or 4 x 8 columns with 8 lanes
+// each 750-1570 us.
+constexpr int kBpTileU = 8, kBpTileV = 32;   // staged rays: one per thread
+template <typename R>
 __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* __restrict__ resid,
                                                              const R* __restrict__ p,
                                                              const R* __restrict__ y,
                                                              R* __restrict__ out)
 {
-    // One staged ray in four 16-byte records (two 32-byte ones in FP64), read
-    // with one wide load each; consecutive rays sit in consecutive records,
-    // so the lanes of a column, which take consecutive rays, read without
-    // bank conflicts.  Axes in column order (A, B, z):
+    // One staged ray in records of consecutive rays, so the lanes of a
+    // column, which take consecutive rays, read without bank conflicts.  Axes
+    // in column order (A, B, z):
     //   s_r0: the sample nearest the brick centre minus the brick origin, r dt
     //   s_r1: the index-space step per sample, slab lower bound along A
-    //   s_r2: slab upper bound along A; lo, hi, 1/step across the column in B
-    //   s_r3: lo, hi, 1/step across the column in z
-    // Slab bounds are in samples: |q_a + m d_a - l| < 1 for m in
-    // (lo_a + l inv_a, hi_a + l inv_a); along A the whole column (-1, 16),
-    // narrowed to the ray's valid samples.
-    __shared__ BPVec4<R> s_r0[256], s_r1[256];
-    __shared__ float4 s_r2[256], s_r3[256];
-    // thread t's run of 21 accumulators: 16 voxels along A at slots [2, 18)
+    //   s_r2: 1/step in B and z; s_r3: slab upper bound along A
+    // Slab bounds are in samples: |q_a + m d_a - l| < 1 for m within |1/d_a|
+    // of (l - q_a) / d_a; along A the whole column (-1, 16), narrowed to the
+    // ray's valid samples.
+    constexpr int TU = kBpTileU, TV = kBpTileV, NR = 256;
+    static_assert(TU * TV == NR, "one staged ray per thread");
+    __shared__ BPVec4<R> s_r0[NR], s_r1[NR];
+    __shared__ float2 s_r2[NR];
+    __shared__ float s_r3[NR];
+    // thread t's run of 20 accumulators: 16 voxels along A at slots [2, 18)
     // (two pad slots each side take the clipped weights of samples just
     // outside the column, so the accumulation needs no branch); slot-major,
     // slot s of thread t at s * 256 + t, so each slot of the 64 lanes of a
     // wave spans all banks and a lane's bank does not depend on the slot:
     // the read-modify-writes never conflict
-    __shared__ R s_acc[21 * 256];
+    __shared__ R s_acc[20 * 256];
     __shared__ int s_box[4];
     const RayGeom& g = A.g;
     const int t = threadIdx.x;
@@ -1600,8 +1618,8 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     // rays of one column, so their record loads hit distinct banks
     const int col = t >> 4, lane = t & 15;        // column (lb, lz) and ray lane
     const int lb = col & 3, lz = col >> 2;
-    for (int e = t; e < 256 * 21; e += 256) s_acc[e] = (R)0;
-    R* acc = s_acc + 2 * 256 + t;
+    for (int e = t; e < 256 * 20; e += 256) s_acc[e] = (R)0;
+    R* acc = s_acc + t;
     if (t == 0) {
         const float lo[3] = {(float)(b0[0] - 1), (float)(b0[1] - 1), (float)(b0[2] - 1)};
         const float hi[3] = {(float)(b0[0] + A.bx), (float)(b0[1] + A.by), (float)(b0[2] + A.bz)};
@@ -1630,10 +1648,10 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     // column rays that cross it alike (the lanes of a wave then run their
     // sample loops for similar lengths: ~0.55 of the lanes busy in the loop
     // against ~0.3 with 16 x 16 tiles, and ~40 % fewer rounds of rays)
-    for (int tv0 = bv0; tv0 <= bv1; tv0 += 32) {
-        for (int tu0 = bu0; tu0 <= bu1; tu0 += 8) {
+    for (int tv0 = bv0; tv0 <= bv1; tv0 += TV) {
+        for (int tu0 = bu0; tu0 <= bu1; tu0 += TU) {
             {   // stage one ray per thread (FP64 set-up, once per ray and brick)
-                const int iu = tu0 + (t & 7), iv = tv0 + (t >> 3);
+                const int iu = tu0 + t % TU, iv = tv0 + t / TU;
                 int m0 = 1, m1 = 0;
                 R rw = (R)0;
                 double qr[3] = {0.0, 0.0, 0.0}, dq[3] = {0.0, 0.0, 0.0};
@@ -1650,12 +1668,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                         L2 += w * w;
                     }
                     if (L2 > 0.0 && r != 0.0) {
-                        // 1/L from the hardware reciprocal square root and two
-                        // Newton steps (each doubles the correct bits)
-                        double invL = __builtin_amdgcn_rsq(L2);
-                        invL = fma(0.5 * invL, fma(-L2 * invL, invL, 1.0), invL);
-                        invL = fma(0.5 * invL, fma(-L2 * invL, invL, 1.0), invL);
-                        const double L = L2 * invL;
+                        const double invL = rsq64(L2), L = L2 * invL;
                         double tc = 0.0;
 #pragma unroll
                         for (int ax = 0; ax < 3; ++ax) {
@@ -1665,8 +1678,8 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                         // the last sample lies at the detector, far outside the
                         // volume, and the centre sample only anchors m: neither
                         // needs a correctly rounded quotient
-                        const double nlast = floor(L * A.inv_dt);
-                        const double nc = fmin(fmax(rint(tc * A.inv_dt), 0.0), nlast);
+                        const double nlast = floor(L * g.inv_dt);
+                        const double nc = fmin(fmax(rint(tc * g.inv_dt), 0.0), nlast);
                         const double tn = nc * g.dt;
 #pragma unroll
                         for (int ax = 0; ax < 3; ++ax) {
@@ -1696,18 +1709,18 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 const float la = fmaxf(lo[AX], (float)m0 - 0.5f), ha = fminf(hi[AX], (float)m1 + 0.5f);
                 s_r0[t] = {(R)qr[AX], (R)qr[BX], (R)qr[2], rw};
                 s_r1[t] = {(R)dq[AX], (R)dq[BX], (R)dq[2], (R)la};
-                s_r2[t] = make_float4(ha, lo[BX], hi[BX], inv[BX]);
-                s_r3[t] = make_float4(lo[2], hi[2], inv[2], 0.0f);
+                s_r2[t] = make_float2(inv[BX], inv[2]);
+                s_r3[t] = ha;
             }
             __syncthreads();
             // rays of this tile inside the column's footprint, split over the
             // column's 16 lanes
-            const int ua = max(ru0, tu0), ub = min(ru1, tu0 + 7);
-            const int va = max(rv0, tv0), vb = min(rv1, tv0 + 31);
+            const int ua = max(ru0, tu0), ub = min(ru1, tu0 + TU - 1);
+            const int va = max(rv0, tv0), vb = min(rv1, tv0 + TV - 1);
             const int wu = ub - ua + 1, nr = (ub >= ua && vb >= va) ? wu * (vb - va + 1) : 0;
             // ray i of the clipped box (row-major) is (i % wu, i / wu); the
             // lane steps i by 16, i.e. (16 % wu, 16 / wu) with one carry
-            const int kb = ((va - tv0) << 3) + (ua - tu0);
+            const int kb = (va - tv0) * TU + (ua - tu0);
             int ou = 0, ov = 0, su = 0, sv = 0;
             if (nr > 0) {
                 ou = lane % wu;
@@ -1716,7 +1729,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 sv = 16 / wu;
             }
             for (int i = lane; i < nr; i += 16) {
-                const int k = kb + (ov << 3) + ou;
+                const int k = kb + ov * TU + ou;
                 ou += su;
                 ov += sv;
                 if (ou >= wu) {
@@ -1727,15 +1740,18 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 // 1e-3 sample slack covers the FP32 rounding of the bounds and
                 // the weights clip any sample it admits)
                 const BPVec4<R> r0 = s_r0[k], r1 = s_r1[k];
-                const float4 r2 = s_r2[k], r3 = s_r3[k];
-                float lo = fmaxf(fmaxf((float)r1.w, fmaf(flb, r2.w, r2.y)), fmaf(flz, r3.z, r3.x));
-                float hi = fminf(fminf(r2.x, fmaf(flb, r2.w, r2.z)), fmaf(flz, r3.z, r3.y));
+                const float2 r2 = s_r2[k];
+                const float ha = s_r3[k];
+                // |q + m d - l| < 1 for m within |1/d| of (l - q) / d
+                const R qa = r0.x + (R)2, qb = r0.y - rlb, qz = r0.z - rlz;
+                const float cb_ = -(float)qb * r2.x, cz_ = -(float)qz * r2.y;
+                float lo = fmaxf(fmaxf((float)r1.w, cb_ - fabsf(r2.x)), cz_ - fabsf(r2.y));
+                float hi = fminf(fminf(ha, cb_ + fabsf(r2.x)), cz_ + fabsf(r2.y));
                 lo = fminf(fmaxf(lo, -1.0e6f), 1.0e6f);   // |m| stays far inside int range
                 hi = fminf(fmaxf(hi, -1.0e6f), 1.0e6f);
                 const int m0 = (int)ceilf(lo - 1.0e-3f);
                 const int m1 = (int)floorf(hi + 1.0e-3f);
                 if (m0 > m1) continue;
-                const R qa = r0.x, qb = r0.y - rlb, qz = r0.z - rlz;
                 const R da = r1.x, db = r1.y, dz = r1.z;
                 const R rw = r0.w;
                 // the sample index runs as a float (|m| < 1e6: exact)
@@ -1745,25 +1761,23 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 // LDS write
                 __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
                 for (R fm = (R)m0; fm <= fm1; fm += (R)1) {
-                    const R wbz = fmax((R)0, (R)1 - fabs(fma(fm, db, qb))) *
-                                  fmax((R)0, (R)1 - fabs(fma(fm, dz, qz))) * rw;
-                    const R xa = fma(fm, da, qa);
-                    const R fl = floor(xa);
-                    // the slab range keeps xa within (-1.01, 16.01); the clamp
+                    // (saturated differences: one instruction each in FP32)
+                    const R wbz = saturate((R)1 - fabs(fma(fm, db, qb))) *
+                                  (saturate((R)1 - fabs(fma(fm, dz, qz))) * rw);
+                    // two voxels into the run, so that truncation is the floor;
+                    // the slab range keeps xa within (0.99, 18.01): the clamp
                     // only guards the LDS run
-                    const int j = min(max((int)fl, -2), 16);
-                    const R fa = xa - fl;
+                    const R xa = fma(fm, da, qa);
+                    const int j = min(max((int)xa, 0), 18);
+                    const R t1 = fract_of(xa) * wbz, t0 = wbz - t1;
                     // the thread's own LDS run: a plain read-modify-write
-                    acc[j * 256] += ((R)1 - fa) * wbz;
-                    acc[(j + 1) * 256] += fa * wbz;
+                    acc[j * 256] += t0;
+                    acc[(j + 1) * 256] += t1;
                 }
             }
             __syncthreads();
         }
     }
-    // voxel (column c, position j along A): the sum over the column's 16
-    // lanes, in an order rotated by j so that the lanes of a wave read
-    // different banks
     {
         const int c = t >> 4, j = t & 15;
         R v = (R)0;
@@ -2378,7 +2392,6 @@ hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeo
     A.a = a;
     A.b = b;
     A.scale = scale;
-    A.inv_dt = 1.0 / rg.dt;
     const long blocks = (long)A.nbx * A.nby * nbz;
     if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
     PCR_DISPATCH_R(compute, R,
