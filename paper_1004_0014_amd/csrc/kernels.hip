@@ -230,8 +230,21 @@ __global__ void __launch_bounds__(256) k_compose(const S* __restrict__ mean,
 }
 
 // --------------------------------------------------------------- warp ----
+// x / s for a grid constant s, given rs = RN(1 / s): a product and one
+// correction step (Markstein), the correctly rounded quotient of a normal
+// result at a third of the instructions of a division.
+template <typename R>
+__device__ __forceinline__ R div_by(R x, R s, R rs)
+{
+    const R q = x * rs;
+    return fma(fma(-q, s, x), rs, q);
+}
+
 // Trilinear sample of an unpadded image at index-space point q, zero outside;
-// optionally also the exact partial derivatives dT/dq (floor cell).
+// optionally also the exact partial derivatives dT/dq (floor cell).  All taps
+// are loaded before the first is used (a branch per tap made each wait for
+// the one before): where every lane's cell lies inside the image, as four
+// pairs along x, else at clamped indices and masked.
 template <typename R, typename S, bool GRAD>
 __device__ __forceinline__ R sample_f0(const S* __restrict__ f0, int nx, int ny, int nz,
                                        R qx, R qy, R qz, R* dT)
@@ -244,18 +257,48 @@ __device__ __forceinline__ R sample_f0(const S* __restrict__ f0, int nx, int ny,
     R ax = qx - fx, ay = qy - fy, az = qz - fz;
     R bx = (R)1 - ax, by = (R)1 - ay, bz = (R)1 - az;
     R c[2][2][2];
+    const bool inside = (unsigned)i0 < (unsigned)(nx - 1) && (unsigned)j0 < (unsigned)(ny - 1) &&
+                        (unsigned)k0 < (unsigned)(nz - 1);
+    if (__all(inside)) {
+        struct Pair {
+            S a, b;
+        } t[2][2];
+        const S* base = f0 + ((size_t)i0 + (size_t)nx * ((size_t)j0 + (size_t)ny * k0));
 #pragma unroll
-    for (int dz = 0; dz < 2; ++dz)
+        for (int dz = 0; dz < 2; ++dz)
 #pragma unroll
-        for (int dy = 0; dy < 2; ++dy)
+            for (int dy = 0; dy < 2; ++dy)
+                __builtin_memcpy(&t[dz][dy], base + ((size_t)nx * (dy + (size_t)ny * dz)), sizeof(Pair));
 #pragma unroll
-            for (int dx = 0; dx < 2; ++dx) {
-                int i = i0 + dx, j = j0 + dy, k = k0 + dz;
-                bool in = (unsigned)i < (unsigned)nx && (unsigned)j < (unsigned)ny &&
-                          (unsigned)k < (unsigned)nz;
-                c[dz][dy][dx] = in ? widen<R>(f0[(size_t)i + (size_t)nx * ((size_t)j + (size_t)ny * k)])
-                                   : (R)0;
+        for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy) {
+                c[dz][dy][0] = widen<R>(t[dz][dy].a);
+                c[dz][dy][1] = widen<R>(t[dz][dy].b);
             }
+    } else {
+        S t[2][2][2];
+#pragma unroll
+        for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 2; ++dx) {
+                    const int i = min(max(i0 + dx, 0), nx - 1), j = min(max(j0 + dy, 0), ny - 1),
+                              k = min(max(k0 + dz, 0), nz - 1);
+                    t[dz][dy][dx] = f0[(size_t)i + (size_t)nx * ((size_t)j + (size_t)ny * k)];
+                }
+#pragma unroll
+        for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+                for (int dx = 0; dx < 2; ++dx) {
+                    const bool in = (unsigned)(i0 + dx) < (unsigned)nx && (unsigned)(j0 + dy) < (unsigned)ny &&
+                                    (unsigned)(k0 + dz) < (unsigned)nz;
+                    c[dz][dy][dx] = in ? widen<R>(t[dz][dy][dx]) : (R)0;
+                }
+    }
     R w00 = by * bz, w10 = ay * bz, w01 = by * az, w11 = ay * az;
     R val = w00 * (bx * c[0][0][0] + ax * c[0][0][1]) + w10 * (bx * c[0][1][0] + ax * c[0][1][1]) +
             w01 * (bx * c[1][0][0] + ax * c[1][0][1]) + w11 * (bx * c[1][1][0] + ax * c[1][1][1]);
@@ -273,7 +316,42 @@ __device__ __forceinline__ R sample_f0(const S* __restrict__ f0, int nx, int ny,
 struct VoxGrid {
     int nx, ny, nz;
     double sp[3];
+    double rd[3];   // 1 / sp, and 1 / (float)sp in FP32 (for div_by)
+    float rf[3];
 };
+template <typename R>
+__device__ __forceinline__ R by_spacing(R x, const VoxGrid& g, int a)
+{
+    if constexpr (std::is_same<R, float>::value) return div_by(x, (float)g.sp[a], g.rf[a]);
+    else return div_by(x, (R)g.sp[a], (R)g.rd[a]);
+}
+
+// Displacement x = mean + sum_k w_k u_k and the fields u_k of one voxel: all
+// loads first, then the sums.  Fields past the K-th (of KM) repeat the last
+// one's loads (from the cache) and are replaced by zero.  O: type of the
+// voxel's byte offset within a field.
+template <typename R, typename S, int KM, typename O>
+__device__ __forceinline__ void load_fields(const S* __restrict__ mean, const S* __restrict__ U, int K, size_t N,
+                                            O off, const Chan<double, 8>& w, R (&x)[3], R (&u)[KM][3])
+{
+    S m[3], f[KM][3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) m[a] = *(const S*)((const char*)(mean + a * N) + off);
+#pragma unroll
+    for (int kk = 0; kk < KM; ++kk)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            f[kk][a] = *(const S*)((const char*)(U + (size_t)(min(kk, K - 1) * 3 + a) * N) + off);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) x[a] = widen<R>(m[a]);
+#pragma unroll
+    for (int kk = 0; kk < KM; ++kk)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            u[kk][a] = kk < K ? widen<R>(f[kk][a]) : (R)0;
+            x[a] += (R)w.v[kk] * u[kk][a];
+        }
+}
 
 // Standalone warp: f[v] = T[f0](v + dvf[v] / s).
 template <typename R, typename S>
@@ -285,50 +363,41 @@ __global__ void __launch_bounds__(256) k_warp_plain(const S* __restrict__ f0,
     if (i >= g.nx || j >= g.ny) return;
     size_t N = (size_t)g.nx * g.ny * g.nz;
     size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-    R qx = (R)i + dvf[v] / (R)g.sp[0];
-    R qy = (R)j + dvf[N + v] / (R)g.sp[1];
-    R qz = (R)k + dvf[2 * N + v] / (R)g.sp[2];
+    const R x0 = dvf[v], x1 = dvf[N + v], x2 = dvf[2 * N + v];
+    R qx = (R)i + by_spacing(x0, g, 0);
+    R qy = (R)j + by_spacing(x1, g, 1);
+    R qz = (R)k + by_spacing(x2, g, 2);
     f[v] = sample_f0<R, S, false>(f0, g.nx, g.ny, g.nz, qx, qy, qz, nullptr);
 }
 
 // Fused compose + warp (+ tangents) of one voxel: channel 0 = f, channels
-// 1..K = h_k = sum_a (1/s_a) dT[f0]/dq_a u_k[a] (tangent), rest zero.
-template <typename R, typename S, typename F, int C, bool TAN>
+// 1..K = h_k = sum_a (1/s_a) dT[f0]/dq_a u_k[a] (tangent), rest zero.  KM: most
+// fields the instance takes.  (FP32 images stay below 2^31 bytes at 4 bytes a
+// voxel or more, so a field's byte offsets fit 32 bits there.)
+template <typename R, typename S, typename F, int C, bool TAN, int KM>
 __device__ __forceinline__ Chan<R, C> warp_cell(const F* __restrict__ f0, const S* __restrict__ mean,
                                                 const S* __restrict__ U, int K,
                                                 const Chan<double, 8>& w, const VoxGrid& g, int i,
                                                 int j, int k)
 {
-    size_t N = (size_t)g.nx * g.ny * g.nz;
-    size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-    R x[3];
-    R u[TAN ? 8 : 1][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) x[a] = widen<R>(mean[a * N + v]);
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        if (kk < K) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                R uv = widen<R>(U[(size_t)(kk * 3 + a) * N + v]);
-                x[a] += (R)w.v[kk] * uv;
-                if (TAN) u[TAN ? kk : 0][a] = uv;
-            }
-        }
-    }
-    R qx = (R)i + x[0] / (R)g.sp[0];
-    R qy = (R)j + x[1] / (R)g.sp[1];
-    R qz = (R)k + x[2] / (R)g.sp[2];
+    using O = typename std::conditional<std::is_same<R, float>::value, unsigned, size_t>::type;
+    const size_t N = (size_t)g.nx * g.ny * g.nz;
+    const O off = ((O)i + (O)g.nx * ((O)j + (O)g.ny * (O)k)) * (O)sizeof(S);
+    R x[3], u[KM][3];
+    load_fields<R, S, KM, O>(mean, U, K, N, off, w, x, u);
+    R qx = (R)i + by_spacing(x[0], g, 0);
+    R qy = (R)j + by_spacing(x[1], g, 1);
+    R qz = (R)k + by_spacing(x[2], g, 2);
     R dT[3];
     Chan<R, C> o;
 #pragma unroll
     for (int c = 0; c < C; ++c) o.v[c] = (R)0;
     o.v[0] = sample_f0<R, F, TAN>(f0, g.nx, g.ny, g.nz, qx, qy, qz, dT);
-    if (TAN) {
-        R G0 = dT[0] / (R)g.sp[0], G1 = dT[1] / (R)g.sp[1], G2 = dT[2] / (R)g.sp[2];
+    if constexpr (TAN) {
+        R G0 = by_spacing(dT[0], g, 0), G1 = by_spacing(dT[1], g, 1), G2 = by_spacing(dT[2], g, 2);
 #pragma unroll
         for (int kk = 0; kk < C - 1; ++kk)
-            if (kk < K) o.v[kk + 1] = G0 * u[TAN ? kk : 0][0] + G1 * u[TAN ? kk : 0][1] + G2 * u[TAN ? kk : 0][2];
+            if (kk < K) o.v[kk + 1] = G0 * u[kk][0] + G1 * u[kk][1] + G2 * u[kk][2];
     }
     return o;
 }
@@ -365,10 +434,14 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
 
 // x-fastest padded layout: a block per 256-voxel run along x, coalesced in x
 // both ways (longer runs than 64 x 4 blocks: 49.5 against 57.7 us at paper
-// scale).  (Ordering the runs by XCD, as the y-fastest tiles are, was 2-4 %
+// scale).  FP32 at paper scale streams 297 MB (4.4 M voxels of 68 bytes) in
+// 49 us, 6 TB/s with part of the model in the Infinity Cache; a BF16 model
+// moves fewer bytes a load and was bound by the chain of waits until all of
+// a voxel's loads went out together (load_fields, sample_f0): K = 4 at
+// 256x256x128 102 -> 69 us, K = 5 at 512x512x160 520 -> 370 us (1.5 GB).  (Ordering the runs by XCD, as the y-fastest tiles are, was 2-4 %
 // slower here: in dispatch order the XCDs work on neighbouring rows at the
 // same time and share their f0 taps through the Infinity Cache.)
-template <typename R, typename S, typename F, int C, bool TAN, bool H>
+template <typename R, typename S, typename F, int C, bool TAN, bool H, int KM>
 __global__ void __launch_bounds__(256) k_warp_fused(const F* __restrict__ f0,
                                                     const S* __restrict__ mean,
                                                     const S* __restrict__ U, int K,
@@ -379,7 +452,7 @@ __global__ void __launch_bounds__(256) k_warp_fused(const F* __restrict__ f0,
     const int i = b.lo[0] + blockIdx.x * 256 + threadIdx.x, j = b.lo[1] + blockIdx.y;
     const int k = b.lo[2] + blockIdx.z;
     if (i >= b.hi[0] || j >= b.hi[1]) return;
-    Chan<R, C> o = warp_cell<R, S, F, C, TAN>(f0, mean, U, K, w, g, i, j, k);
+    Chan<R, C> o = warp_cell<R, S, F, C, TAN, KM>(f0, mean, U, K, w, g, i, j, k);
     out[(size_t)(i + 1) + (size_t)px * ((size_t)(j + 1) + (size_t)py * (k + 1))] =
         store_cell<R, C, H>(o, hs);
 }
@@ -398,7 +471,7 @@ constexpr int yf_tile_x()
 // y-fastest padded layout: a TX x 8 (x, y) tile per block, computed with
 // x-contiguous reads (runs of 4 TX bytes of each field), staged in LDS and
 // written as 8-cell runs along y.
-template <typename R, typename S, typename F, int C, bool TAN, bool H>
+template <typename R, typename S, typename F, int C, bool TAN, bool H, int KM>
 __global__ void __launch_bounds__(256) k_warp_fused_yf(const F* __restrict__ f0,
                                                        const S* __restrict__ mean,
                                                        const S* __restrict__ U, int K,
@@ -421,7 +494,7 @@ __global__ void __launch_bounds__(256) k_warp_fused_yf(const F* __restrict__ f0,
         const int il = t % TX, jl = t / TX + (256 / TX) * r;
         const int i = i0 + il, j = j0 + jl;
         if (i < b.hi[0] && j < b.hi[1])
-            tile[jl][il] = store_cell<R, C, H>(warp_cell<R, S, F, C, TAN>(f0, mean, U, K, w, g, i, j, k), hs);
+            tile[jl][il] = store_cell<R, C, H>(warp_cell<R, S, F, C, TAN, KM>(f0, mean, U, K, w, g, i, j, k), hs);
     }
     __syncthreads();
 #pragma unroll
@@ -1793,7 +1866,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
 
 // ---------------------------------------------------------- contraction --
 // partials[k * blocks + block] = sum_v g[v] * sum_a (1/s_a) dT[f0]/dq_a(q_v) u_k[a][v]
-template <typename R, typename S, typename F>
+template <typename R, typename S, typename F, int KM>
 __global__ void __launch_bounds__(256) k_contract(const F* __restrict__ f0,
                                                   const S* __restrict__ mean,
                                                   const S* __restrict__ U, int K,
@@ -1802,46 +1875,37 @@ __global__ void __launch_bounds__(256) k_contract(const F* __restrict__ f0,
                                                   double* __restrict__ partials)
 {
     const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y;
-    double m[8];
+    double m[KM];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) m[kk] = 0.0;
+    for (int kk = 0; kk < KM; ++kk) m[kk] = 0.0;
     for (int k = blockIdx.z; k < g.nz; k += gridDim.z) {
     if (i < g.nx && j < g.ny) {
         size_t N = (size_t)g.nx * g.ny * g.nz;
         size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
         R gv = gpad[v];
         if (gv != (R)0) {
-            R x[3], u[8][3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a) x[a] = widen<R>(mean[a * N + v]);
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
-                if (kk < K)
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        u[kk][a] = widen<R>(U[(size_t)(kk * 3 + a) * N + v]);
-                        x[a] += (R)w.v[kk] * u[kk][a];
-                    }
-            R qx = (R)i + x[0] / (R)g.sp[0];
-            R qy = (R)j + x[1] / (R)g.sp[1];
-            R qz = (R)k + x[2] / (R)g.sp[2];
+            R x[3], u[KM][3];
+            load_fields<R, S, KM, size_t>(mean, U, K, N, v * sizeof(S), w, x, u);
+            R qx = (R)i + by_spacing(x[0], g, 0);
+            R qy = (R)j + by_spacing(x[1], g, 1);
+            R qz = (R)k + by_spacing(x[2], g, 2);
             R dT[3];
             sample_f0<R, F, true>(f0, g.nx, g.ny, g.nz, qx, qy, qz, dT);
             double G0 = (double)dT[0] / g.sp[0], G1 = (double)dT[1] / g.sp[1],
                    G2 = (double)dT[2] / g.sp[2];
             double gd = (double)gv;
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
+            for (int kk = 0; kk < KM; ++kk)
                 if (kk < K)
                     m[kk] += gd * (G0 * (double)u[kk][0] + G1 * (double)u[kk][1] + G2 * (double)u[kk][2]);
         }
     }
     }
     // threadIdx is 2-D (64 x 4): flatten for the block reduction
-    __shared__ double red[4][8];
+    __shared__ double red[4][KM];
     const int lane = threadIdx.x, wv = threadIdx.y;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < KM; ++kk) {
         double s = wave_sum(m[kk]);
         if (lane == 0) red[wv][kk] = s;
     }
@@ -1866,9 +1930,9 @@ __global__ void __launch_bounds__(256) k_warp_adjoint(const R* __restrict__ dvf,
     size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
     R val = gv[v];
     if (val == (R)0) return;
-    R qx = (R)i + dvf[v] / (R)g.sp[0];
-    R qy = (R)j + dvf[N + v] / (R)g.sp[1];
-    R qz = (R)k + dvf[2 * N + v] / (R)g.sp[2];
+    R qx = (R)i + by_spacing(dvf[v], g, 0);
+    R qy = (R)j + by_spacing(dvf[N + v], g, 1);
+    R qz = (R)k + by_spacing(dvf[2 * N + v], g, 2);
     qx = clampv(qx, (R)-2, (R)(g.nx + 1));
     qy = clampv(qy, (R)-2, (R)(g.ny + 1));
     qz = clampv(qz, (R)-2, (R)(g.nz + 1));
@@ -1970,7 +2034,11 @@ static VoxGrid vox(const pcr_grid& g)
     v.nx = g.n[0];
     v.ny = g.n[1];
     v.nz = g.n[2];
-    for (int a = 0; a < 3; ++a) v.sp[a] = g.spacing_mm[a];
+    for (int a = 0; a < 3; ++a) {
+        v.sp[a] = g.spacing_mm[a];
+        v.rd[a] = 1.0 / g.spacing_mm[a];
+        v.rf[a] = 1.0f / (float)g.spacing_mm[a];
+    }
     return v;
 }
 static dim3 vox_grid(const pcr_grid& g)
@@ -2142,35 +2210,39 @@ static hipError_t warp_fused_c(const pcr_grid& g, const PadLayout& L, int K, boo
     if ((long)((ex + 31) / 32) * gyy * ez > 0x7fffffffL) return hipErrorInvalidValue;
     Chan<float, 8> hs;
     for (int c = 0; c < 8; ++c) hs.v[c] = L.hs[c];
-#define PCR_WF2(C, T, H)                                                                          \
-    (L.yfast ? k_warp_fused_yf<R, S, F, C, T, H><<<grid_yf(yf_tile_x<R, C, H>()), 256, 0, s>>>(  \
+#define PCR_WF2(C, T, H, KM)                                                                      \
+    (L.yfast ? k_warp_fused_yf<R, S, F, C, T, H, KM><<<grid_yf(yf_tile_x<R, C, H>()), 256, 0, s>>>( \
                    (const F*)f0, (const S*)mean, (const S*)U, K, w, vox(g), L.px, L.py, hs, b,    \
                    (ex + yf_tile_x<R, C, H>() - 1) / yf_tile_x<R, C, H>(), gyy,                   \
                    (CellOf<R, C, H>*)padded)                                                      \
-             : k_warp_fused<R, S, F, C, T, H><<<grid, blk, 0, s>>>(                               \
+             : k_warp_fused<R, S, F, C, T, H, KM><<<grid, blk, 0, s>>>(                           \
                    (const F*)f0, (const S*)mean, (const S*)U, K, w, vox(g), L.px, L.py, hs, b,    \
                    (CellOf<R, C, H>*)padded))
-#define PCR_WF(C, T) (L.half ? PCR_WF2(C, T, true) : PCR_WF2(C, T, false))
+#define PCR_WF(C) (L.half ? PCR_WF2(C, true, true, C - 1) : PCR_WF2(C, true, false, C - 1))
+#define PCR_WI(KM)                                                                                \
+    k_warp_fused<R, S, F, 1, false, false, KM><<<grid, blk, 0, s>>>(                              \
+        (const F*)f0, (const S*)mean, (const S*)U, K, w, vox(g), L.px, L.py, hs, b, (CellOf<R, 1, false>*)padded)
     if (L.half && !std::is_same<R, float>::value) return hipErrorInvalidValue;
     if (K < 1 || K > 8 || (tangent && K > L.C - 1)) return hipErrorInvalidValue;
     if (!tangent) {
-        switch (L.C) {
-        case 1: PCR_WF(1, false); break;
-        case 2: PCR_WF(2, false); break;
-        case 4: PCR_WF(4, false); break;
-        case 6: PCR_WF(6, false); break;
-        case 8: PCR_WF(8, false); break;
-        default: return hipErrorInvalidValue;
-        }
+        // the image alone: one channel, x-fastest
+        if (L.C != 1 || L.half || L.yfast) return hipErrorInvalidValue;
+        if (K <= 3) PCR_WI(3);
+        else if (K <= 5) PCR_WI(5);
+        else PCR_WI(8);
     } else {
         switch (L.C) {
-        case 2: PCR_WF(2, true); break;
-        case 4: PCR_WF(4, true); break;
-        case 6: PCR_WF(6, true); break;
-        case 8: PCR_WF(8, true); break;
+        case 2: PCR_WF(2); break;
+        case 4: PCR_WF(4); break;
+        case 6:
+            if (L.half) return hipErrorInvalidValue;
+            PCR_WF2(6, true, false, 5);
+            break;
+        case 8: PCR_WF(8); break;
         default: return hipErrorInvalidValue;
         }
     }
+#undef PCR_WI
 #undef PCR_WF
 #undef PCR_WF2
     return hipGetLastError();
@@ -2406,10 +2478,14 @@ hipError_t launch_contract(pcr_dtype compute, pcr_dtype storage, pcr_dtype f0_dt
                            hipStream_t s)
 {
     auto w = wvec(w_eff, K);
+#define PCR_CT(KM)                                                                                \
+    k_contract<R, S, F, KM><<<contract_grid(g), dim3(64, 4), 0, s>>>(                             \
+        (const F*)f0, (const S*)mean, (const S*)U, K, w, vox(g), (const R*)gv, partials)
     PCR_DISPATCH_R(compute, R, PCR_DISPATCH_S(storage, S, PCR_DISPATCH_S(f0_dtype, F,
-        k_contract<R, S, F><<<contract_grid(g), dim3(64, 4), 0, s>>>((const F*)f0, (const S*)mean,
-                                                                (const S*)U, K, w, vox(g),
-                                                                (const R*)gv, partials))));
+        if (K <= 3) PCR_CT(3);
+        else if (K <= 5) PCR_CT(5);
+        else PCR_CT(8))));
+#undef PCR_CT
     return hipGetLastError();
 }
 
