@@ -188,9 +188,15 @@ __global__ void __launch_bounds__(1024) k_reduce(const double* __restrict__ part
     const int nout = nm + (extra >= 0 ? 1 : 0);
     for (int o = wv; o < nout; o += 16) {
         const double* r = part + (size_t)(o < nm ? o : extra) * nblocks;
+        // 16 loads in flight a lane (past the end: the last block's, not added)
         double s = 0.0;
-#pragma unroll 8
-        for (int b = lane; b < nblocks; b += 64) s += r[b];
+        for (int b0 = lane; b0 < nblocks; b0 += 64 * 16) {
+            double v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = r[min(b0 + 64 * i, nblocks - 1)];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += b0 + 64 * i < nblocks ? v[i] : 0.0;
+        }
         s = wave_sum(s);
         if (lane == 0) {
             if (done) __hip_atomic_store(&out[o], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -214,18 +220,45 @@ static hipError_t run_reduce(const double* part, int nblocks, int nm, int extra,
 }
 
 // ------------------------------------------------------------ compose ----
-template <typename R, typename S>
-__global__ void __launch_bounds__(256) k_compose(const S* __restrict__ mean,
-                                                 const S* __restrict__ U, int K, size_t N,
+// dvf = mean + sum_k w_k U_k over the E = 3 N values of a field (the components
+// follow each other, so fields add value by value).  Four values a thread,
+// every field's loads before the first sum: bound by HBM.  A field of odd
+// length leaves the next one unaligned: the wide loads ask for the element's
+// alignment only.  FP16 model, 255x251x99, K = 3: 82 -> 34 us (228 MB);
+// FP32, 256x256x100: 81 -> 67 us (394 MB).
+template <typename R, typename S, int K>
+__global__ void __launch_bounds__(256) k_compose(const S* __restrict__ mean, const S* __restrict__ U, size_t E,
                                                  Chan<double, 8> w, R* __restrict__ dvf)
 {
-    size_t v = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (v >= N) return;
+    constexpr int V = 4;
+    struct Vec {
+        S v[V];
+    };
+    const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * V;
+    if (e >= E) return;
+    if (e + V <= E) {
+        Vec m, f[K];
+        __builtin_memcpy(&m, mean + e, sizeof m);
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        R x = widen<R>(mean[a * N + v]);
-        for (int k = 0; k < K; ++k) x += (R)w.v[k] * widen<R>(U[(size_t)(k * 3 + a) * N + v]);
-        dvf[a * N + v] = x;
+        for (int k = 0; k < K; ++k) __builtin_memcpy(&f[k], U + (size_t)k * E + e, sizeof m);
+        struct {
+            R v[V];
+        } o;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            R x = widen<R>(m.v[i]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) x += (R)w.v[k] * widen<R>(f[k].v[i]);
+            o.v[i] = x;
+        }
+        __builtin_memcpy(dvf + e, &o, sizeof o);
+    } else {
+        for (size_t i = e; i < E; ++i) {
+            R x = widen<R>(mean[i]);
+#pragma unroll
+            for (int k = 0; k < K; ++k) x += (R)w.v[k] * widen<R>(U[(size_t)k * E + i]);
+            dvf[i] = x;
+        }
     }
 }
 
@@ -1919,39 +1952,75 @@ __global__ void __launch_bounds__(256) k_contract(const F* __restrict__ f0,
 }
 
 // -------------------------------------------------------- warp adjoint ---
+// Lane l's value from lane l - 1 (lane 0: its own) of the wave.
+template <typename T>
+__device__ __forceinline__ T from_left(T v)
+{
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    int w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof v);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i)
+        w[i] = __builtin_amdgcn_update_dpp(w[i], w[i], 0x138, 0xf, 0xf, false);   // wave_shr:1
+    __builtin_memcpy(&v, w, sizeof v);
+    return v;
+}
+
+// W^T g by atomics, bound by their number: neighbouring voxels along x mostly
+// fall in neighbouring cells, so a lane hands its four sums for the cell's
+// right side to the next lane where that one's cell follows its own, and
+// most lanes issue four atomics instead of eight.  256x256x100: 164 -> 120 us.
 template <typename R>
 __global__ void __launch_bounds__(256) k_warp_adjoint(const R* __restrict__ dvf,
                                                       const R* __restrict__ gv, VoxGrid g,
                                                       R* __restrict__ out)
 {
-    int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= g.nx || j >= g.ny) return;
-    size_t N = (size_t)g.nx * g.ny * g.nz;
-    size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-    R val = gv[v];
-    if (val == (R)0) return;
+    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
+    if (j >= g.ny) return;   // whole waves: a wave is one row of voxels
+    const bool in = i < g.nx;
+    const size_t N = (size_t)g.nx * g.ny * g.nz;
+    const size_t v = (size_t)(in ? i : g.nx - 1) + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
+    const R val = in ? gv[v] : (R)0;
+    if (__all(val == (R)0)) return;
     R qx = (R)i + by_spacing(dvf[v], g, 0);
     R qy = (R)j + by_spacing(dvf[N + v], g, 1);
     R qz = (R)k + by_spacing(dvf[2 * N + v], g, 2);
     qx = clampv(qx, (R)-2, (R)(g.nx + 1));
     qy = clampv(qy, (R)-2, (R)(g.ny + 1));
     qz = clampv(qz, (R)-2, (R)(g.nz + 1));
-    R fx = floor(qx), fy = floor(qy), fz = floor(qz);
-    int i0 = (int)fx, j0 = (int)fy, k0 = (int)fz;
-    R ax = qx - fx, ay = qy - fy, az = qz - fz;
-    R wx[2] = {(R)1 - ax, ax}, wy[2] = {(R)1 - ay, ay}, wz[2] = {(R)1 - az, az};
+    const R fx = floor(qx), fy = floor(qy), fz = floor(qz);
+    const int i0 = (int)fx, j0 = (int)fy, k0 = (int)fz;
+    const R ax = qx - fx, ay = qy - fy, az = qz - fz;
+    const R bx = (R)1 - ax, by = (R)1 - ay, bz = (R)1 - az;
+    // (products in the order x, y, z; a zero value adds nothing anywhere)
+    const bool on = val != (R)0;
+    const R w[4] = {by * bz, ay * bz, by * az, ay * az};
+    R lo[4], hi[4];
 #pragma unroll
-    for (int dz = 0; dz < 2; ++dz)
+    for (int r = 0; r < 4; ++r) {
+        lo[r] = on ? bx * w[r] * val : (R)0;
+        hi[r] = on ? ax * w[r] * val : (R)0;
+    }
+    const int lane = threadIdx.x;
+    // (all lanes take part in each exchange: none inside a condition)
+    const int li = from_left(i0), lj = from_left(j0), lk = from_left(k0);
+    const bool take = (lane > 0) & (li + 1 == i0) & (lj == j0) & (lk == k0);
+    // whether the next lane takes this one's right side (the last has none)
+    const bool given = ((__ballot(take) >> 1) >> lane) & 1u;
 #pragma unroll
-        for (int dy = 0; dy < 2; ++dy)
+    for (int r = 0; r < 4; ++r) {
+        const R h = from_left(hi[r]);
+        lo[r] += take ? h : (R)0;
+    }
 #pragma unroll
-            for (int dx = 0; dx < 2; ++dx) {
-                int ii = i0 + dx, jj = j0 + dy, kk = k0 + dz;
-                if ((unsigned)ii < (unsigned)g.nx && (unsigned)jj < (unsigned)g.ny &&
-                    (unsigned)kk < (unsigned)g.nz)
-                    unsafeAtomicAdd(out + ((size_t)ii + (size_t)g.nx * ((size_t)jj + (size_t)g.ny * kk)),
-                                    wx[dx] * wy[dy] * wz[dz] * val);
-            }
+    for (int r = 0; r < 4; ++r) {
+        const int jj = j0 + (r & 1), kk = k0 + (r >> 1);
+        if ((unsigned)jj < (unsigned)g.ny && (unsigned)kk < (unsigned)g.nz) {
+            R* row = out + (size_t)g.nx * ((size_t)jj + (size_t)g.ny * kk);
+            if ((unsigned)i0 < (unsigned)g.nx && lo[r] != (R)0) unsafeAtomicAdd(row + i0, lo[r]);
+            if (!given && (unsigned)(i0 + 1) < (unsigned)g.nx && hi[r] != (R)0) unsafeAtomicAdd(row + i0 + 1, hi[r]);
+        }
+    }
 }
 
 // ------------------------------------------------------------ localise ---
@@ -1991,12 +2060,10 @@ __global__ void __launch_bounds__(64) k_localize(const S* __restrict__ mean,
                         (dz ? ph[2] : 1.0 - ph[2]);
             if (wt != 0.0) {
                 size_t v = (size_t)(i0[0] + dx) + (size_t)g.nx * ((size_t)(i0[1] + dy) + (size_t)g.ny * (i0[2] + dz));
+                double x[3], u[8][3];
+                load_fields<double, S, 8, size_t>(mean, U, K, N, v * sizeof(S), w, x, u);
 #pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    double x = widen<double>(mean[a * N + v]);
-                    for (int k = 0; k < K; ++k) x += w.v[k] * widen<double>(U[(size_t)(k * 3 + a) * N + v]);
-                    X[a] = wt * x;
-                }
+                for (int a = 0; a < 3; ++a) X[a] = wt * x[a];
             }
         }
         // fixed-order sum over the 8 corners
@@ -2172,11 +2239,18 @@ hipError_t launch_compose(pcr_dtype compute, pcr_dtype storage, const pcr_grid& 
                           const void* mean, const void* U, const double* w_eff, void* dvf,
                           hipStream_t s)
 {
-    size_t N = (size_t)g.n[0] * g.n[1] * g.n[2];
-    unsigned blocks = (unsigned)((N + 255) / 256);
+    const size_t E = 3 * (size_t)g.n[0] * g.n[1] * g.n[2];
+    const unsigned blocks = (unsigned)((E + 1023) / 1024);
+#define PCR_CO(KK)                                                                                \
+    case KK:                                                                                      \
+        k_compose<R, S, KK><<<blocks, 256, 0, s>>>((const S*)mean, (const S*)U, E, wvec(w_eff, K), (R*)dvf); \
+        break;
     PCR_DISPATCH_R(compute, R, PCR_DISPATCH_S(storage, S,
-        k_compose<R, S><<<blocks, 256, 0, s>>>((const S*)mean, (const S*)U, K, N, wvec(w_eff, K),
-                                               (R*)dvf)));
+        switch (K) {
+            PCR_CO(1) PCR_CO(2) PCR_CO(3) PCR_CO(4) PCR_CO(5) PCR_CO(6) PCR_CO(7) PCR_CO(8)
+        default: return hipErrorInvalidValue;
+        }));
+#undef PCR_CO
     return hipGetLastError();
 }
 

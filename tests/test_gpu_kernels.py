@@ -35,3 +35,30 @@ def test_staged_march_box_shapes(n, sp, nu, nv, du, step, ang):
     x_t, x = rounded(S.seeded(3, g.shape, "uniform"), torch.float32)
     p = L.forward_project(g, G, x_t.to(DEV)).cpu().numpy()
     assert rel_l2(p, oracle.project(g, G, x)) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [(1, 1, 1), (5, 1, 1), (67, 3, 2), (64, 5, 4), (130, 7, 3)])
+@pytest.mark.parametrize("K", [1, 4, 8])
+@pytest.mark.parametrize("storage", [torch.float32, torch.bfloat16])
+def test_voxel_passes_at_row_ends(n, K, storage):
+    """Composition in vectors of four with a remainder, the warp's taps inside
+    and across the image's edges, its transpose with lanes that hand their
+    right side on, and K up to 8, on rows shorter and longer than a wave.
+    FP32 chains of K + 1 products and of 8 taps: bounds of 1e-6 and 1e-5."""
+    L = _lib()
+    g = S.Grid(n, (2.0, 3.0, 1.5))
+    rng = np.random.default_rng(7)
+    mean_t, mean = rounded(rng.uniform(-3, 3, (3,) + g.shape), storage)
+    U_t, U = rounded(rng.uniform(-1, 1, (K, 3) + g.shape), storage)
+    f_t, f = rounded(rng.uniform(0, 1, g.shape), storage)
+    w = rng.uniform(-2, 2, K)
+    x = L.dvf_compose(g, L.DeviceModel(mean_t.to(DEV), U_t.to(DEV)), w)
+    assert rel_l2(x.cpu().numpy(), oracle.compose(g, mean, U, w)) <= 1e-6
+    x64 = x.double().cpu().numpy()
+    ref = oracle.warp(g, f, x64)
+    got = L.warp_volume(g, f_t.to(DEV), x).cpu().numpy()
+    assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(f)
+    v = torch.tensor(rng.standard_normal(g.shape), dtype=torch.float32)
+    adj = L.warp_adjoint(g, x, v.to(DEV)).cpu().numpy()
+    refa = oracle.warp_adjoint(g, x64, v.double().numpy())
+    assert np.linalg.norm(adj - refa) <= 1e-5 * np.linalg.norm(v.numpy())
