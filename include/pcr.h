@@ -207,8 +207,9 @@ pcr_status pcr_warp_contract(const pcr_grid* grid, const pcr_model* model, pcr_d
 
 /* Forward projection P vol (eq. (2)'s projection matrix, discretised as in
  * the conventions above).  vol_dev [N] and proj_dev [nv][nu] of dtype
- * `compute` (F32 or F64); proj_dev is overwritten.  Allocates a padded
- * device copy of the volume per call (library-owned scratch, reused). */
+ * `compute` (F32 or F64); proj_dev is overwritten.  FP64 and coarse
+ * detectors march a zero-padded device copy of the volume (library-owned
+ * scratch, reused). */
 pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom,
                                pcr_dtype compute, const void* vol_dev, void* proj_dev,
                                void* stream);
@@ -223,8 +224,8 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom,
  * each GPU the library runs on holds it until the process ends; its device
  * address is looked up once per GPU on the first call there.  A grid whose
  * padded copy exceeds the array returns PCR_EINVAL before any launch.  Every
- * call on one GPU shares the array (and clears and refills it): calls that
- * overlap on one GPU (other host threads, or streams not ordered with each
+ * call on one GPU shares the array (and refills it): calls that overlap on
+ * one GPU (other host threads, or streams not ordered with each
  * other) race and give undefined projections.  Not timed by the kernel
  * profiler (pcr_profile_enable), which records events. */
 #define PCR_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)

@@ -309,7 +309,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     y = y_;
     mode = mode_;
     rg = make_ray_geom(*grid, G);
-    ms = choose_march_shape(rg);
+    ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
     M = G.nu * G.nv;
     blocks = march_blocks(rg, ms);
     const bool yfast = prefer_yfast(G);
@@ -326,7 +326,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     }
     sc->L1 = make_pad(*grid, 1);
     rgc = make_ray_geom(*grid, G, yfast);
-    msc = choose_march_shape(rgc);
+    msc = choose_march_shape(rgc, compute == PCR_F32 && !sc->Lc.half ? sc->Lc.C : 0);
     blocksc = march_blocks(rgc, msc);
     const int dev = sc->device;
     if (mode == PCR_GRAD_FUSED) {
@@ -358,7 +358,12 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     PCR_TRY(sc->partials.ensure((size_t)std::max(std::max(blocks, blocksc), cblocks) * kMaxMoments *
                                     sizeof(double),
                                 dev, s));
-    PCR_TRY(sc->moments.ensure(kMaxMoments * sizeof(double), dev, s));
+    // the moments, then the word in which the final sum's workgroups count
+    // themselves (zero between launches)
+    if (!sc->moments.p) {
+        PCR_TRY(sc->moments.ensure((kMaxMoments + 1) * sizeof(double), dev, s));
+        HIP_TRY(launch_zero(sc->moments.p, sc->moments.bytes, s));
+    }
     PCR_TRY(sc->host.ensure(kHostSlots));
     return PCR_OK;
 }
@@ -540,6 +545,7 @@ pcr_status Evaluator::enqueue_eval(const double* w)
     // then publishes this evaluation's sequence number there
     double* mom = sc->host.d;
     unsigned long long* done = (unsigned long long*)(sc->host.d + kDoneSlot);
+    unsigned* arrived = (unsigned*)((double*)sc->moments.p + kMaxMoments);
     const unsigned long long seq = ++sc->seq;
     RayGeom gc = rgc, g1 = rg;
     int vbox[6];
@@ -559,7 +565,7 @@ pcr_status Evaluator::enqueue_eval(const double* w)
         {
             PROF(MARCH, s);
             HIP_TRY(launch_march(compute, sc->Lc, kc, gc, msc, sc->volc.p, y, nullptr,
-                                 (double*)sc->partials.p, mom, done, seq, s));
+                                 (double*)sc->partials.p, mom, arrived, done, seq, s));
         }
     } else {
         {
@@ -570,7 +576,7 @@ pcr_status Evaluator::enqueue_eval(const double* w)
         {
             PROF(MARCH, s);
             HIP_TRY(launch_march(compute, sc->L1, 1, g1, ms, sc->vol1.p, y, sc->p.p,
-                                 (double*)sc->partials.p, mom, done, seq, s));
+                                 (double*)sc->partials.p, mom, arrived, done, seq, s));
         }
     }
     return PCR_OK;
@@ -817,24 +823,24 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     PCR_TRY(check_march_image(*grid, 1, compute));
     PCR_TRY(check_march_steps(*grid, *geom, compute));
     hipStream_t s = (hipStream_t)stream;
+    const PadLayout L = make_pad(*grid, 1);
+    const RayGeom rg = make_ray_geom(*grid, *geom);
+    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
+    if (project_unpadded(compute, rg)) {
+        PROF(MARCH, s);
+        HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
+        return PCR_OK;
+    }
     int dev;
     PCR_TRY(current_device(&dev));
-    PadLayout L = make_pad(*grid, 1);
-    size_t bytes = L.cells() * dtype_size(compute);
-    PCR_TRY(tls.pad.ensure(bytes, dev, s));
-    {
-        PROF(ZERO, s);
-        HIP_TRY(launch_zero(tls.pad.p, bytes, s));
-    }
+    PCR_TRY(tls.pad.ensure(L.cells() * dtype_size(compute), dev, s));
     {
         PROF(PAD, s);
         HIP_TRY(launch_pad(compute, L, vol_dev, tls.pad.p, s));
     }
-    RayGeom rg = make_ray_geom(*grid, *geom);
-    MarchShape ms = choose_march_shape(rg);
     PROF(MARCH, s);
-    HIP_TRY(launch_march(compute, L, 1, rg, ms, tls.pad.p, nullptr, proj_dev, nullptr, nullptr, nullptr, 0,
-                         s));
+    HIP_TRY(launch_march(compute, L, 1, rg, ms, tls.pad.p, nullptr, proj_dev, nullptr, nullptr, nullptr,
+                         nullptr, 0, s));
     return PCR_OK;
 }
 
@@ -855,16 +861,19 @@ pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geo
                     "the fixed scratch array",
                     grid->n[0], grid->n[1], grid->n[2], bytes, (size_t)PCR_NOALLOC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
+    const RayGeom rg = make_ray_geom(*grid, *geom);
+    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
+    if (project_unpadded(compute, rg)) {
+        HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
+        return PCR_OK;
+    }
     int dev;
     PCR_TRY(current_device(&dev));
     void* pad = nullptr;
     PCR_TRY(scratch_on_device(dev, &pad));
-    // the array keeps the previous call's contents: clear the border cells
-    HIP_TRY(launch_zero(pad, bytes, s));
     HIP_TRY(launch_pad(compute, L, vol_dev, pad, s));
-    RayGeom rg = make_ray_geom(*grid, *geom);
-    MarchShape ms = choose_march_shape(rg);
-    HIP_TRY(launch_march(compute, L, 1, rg, ms, pad, nullptr, proj_dev, nullptr, nullptr, nullptr, 0, s));
+    HIP_TRY(launch_march(compute, L, 1, rg, ms, pad, nullptr, proj_dev, nullptr, nullptr, nullptr, nullptr, 0,
+                         s));
     return PCR_OK;
 }
 

@@ -150,14 +150,14 @@ __device__ __forceinline__ void block_sum_store(double (&m)[NM], int nm, double*
 }
 
 // The ray segments' sums (and sample counts) into segment 0's thread of
-// each ray (threads [0, rpb)); smem holds 256 (C + 1) words.  Afterwards
+// each ray (threads [0, rpb)); smem holds T (C + 1) words.  Afterwards
 // only segment 0 holds data: the block's moments need only its waves.
-template <int C>
+template <int C, int T>
 __device__ __forceinline__ void gather_segments(char* smem, int seg, int rpb, int sid, float (&acc)[C],
                                                 int& nsamp)
 {
     float* segbuf = (float*)smem;
-    int* segn = (int*)(segbuf + 256 * C);
+    int* segn = (int*)(segbuf + T * C);
 #pragma unroll
     for (int c = 0; c < C; ++c) segbuf[threadIdx.x * C + c] = acc[c];
     segn[threadIdx.x] = nsamp;
@@ -172,50 +172,54 @@ __device__ __forceinline__ void gather_segments(char* smem, int seg, int rpb, in
 
 // Sum over the blocks of their partial sums, stored slot-major: part[m *
 // nblocks + b] is slot m of block b.  out[0..nm) = sums of slots 0..nm-1;
-// with extra >= 0 also out[nm] = the sum of slot `extra`.  One wave per
-// output: lane l adds blocks l, l + 64, ... in order (coalesced loads), then
-// a fixed shuffle tree: deterministic.
-// With done != null the sums are stored at system scope (through to memory),
-// every wave waits for its stores to complete, and after the block barrier
-// `seq` is stored into *done with a system-scope release: a host polling
-// *done in mapped memory sees the sums once it sees seq.  One release fence
-// per launch, not one per wave.
-__global__ void __launch_bounds__(1024) k_reduce(const double* __restrict__ part, int nblocks, int nm,
-                                                 int extra, double* __restrict__ out,
-                                                 unsigned long long* done, unsigned long long seq)
+// with extra >= 0 also out[nm] = the sum of slot `extra`.  One workgroup per
+// output, 16 KB of loads in flight: a single workgroup for all of them was
+// bound by what one CU can read (16 outputs of 3072 partials: 7.5 -> 4.5 us,
+// 21 of 12288: 10 -> 4.3 us).  Thread t adds blocks t, t + 256, ... in order,
+// then a fixed tree: deterministic.
+// With done != null the sums are stored at system scope (through to memory);
+// each workgroup waits for its store to complete and then counts itself in
+// `arrived` (which wraps to zero at the last, so it is ready for the next
+// launch), and the last one stores `seq` into *done with a system-scope
+// release: a host polling *done in mapped memory sees the sums once it sees
+// seq.  One release fence per launch, not one per workgroup.
+__global__ void __launch_bounds__(256) k_reduce(const double* __restrict__ part, int nblocks, int nm,
+                                                int extra, double* __restrict__ out, unsigned* arrived,
+                                                unsigned long long* done, unsigned long long seq)
 {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int nout = nm + (extra >= 0 ? 1 : 0);
-    for (int o = wv; o < nout; o += 16) {
-        const double* r = part + (size_t)(o < nm ? o : extra) * nblocks;
-        // 16 loads in flight a lane (past the end: the last block's, not added)
-        double s = 0.0;
-        for (int b0 = lane; b0 < nblocks; b0 += 64 * 16) {
-            double v[16];
+    __shared__ double red[4];
+    const int o = blockIdx.x;
+    const double* r = part + (size_t)(o < nm ? o : extra) * nblocks;
+    double s = 0.0;
+    for (int b0 = threadIdx.x; b0 < nblocks; b0 += 256 * 8) {
+        // (past the end: the last block's partial, not added)
+        double v[8];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = r[min(b0 + 64 * i, nblocks - 1)];
+        for (int i = 0; i < 8; ++i) v[i] = r[min(b0 + 256 * i, nblocks - 1)];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s += b0 + 64 * i < nblocks ? v[i] : 0.0;
-        }
-        s = wave_sum(s);
-        if (lane == 0) {
-            if (done) __hip_atomic_store(&out[o], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            else out[o] = s;
-        }
+        for (int i = 0; i < 8; ++i) s += b0 + 256 * i < nblocks ? v[i] : 0.0;
     }
-    if (done) {
-        // every wave waits for its own stores to complete (the barrier alone
-        // does not), then one system-scope release publishes seq
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        if (threadIdx.x == 0) __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    s = ((red[0] + red[1]) + red[2]) + red[3];
+    if (!done) {
+        out[o] = s;
+        return;
     }
+    __hip_atomic_store(&out[o], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __builtin_amdgcn_s_waitcnt(0);   // the store is complete
+    asm volatile("" ::: "memory");
+    if (atomicInc(arrived, gridDim.x - 1) == gridDim.x - 1)
+        __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-static hipError_t run_reduce(const double* part, int nblocks, int nm, int extra, double* out,
-                             hipStream_t s, unsigned long long* done = nullptr, unsigned long long seq = 0)
+static hipError_t run_reduce(const double* part, int nblocks, int nm, int extra, double* out, hipStream_t s,
+                             unsigned* arrived = nullptr, unsigned long long* done = nullptr,
+                             unsigned long long seq = 0)
 {
-    k_reduce<<<1, 1024, 0, s>>>(part, nblocks, nm, extra, out, done, seq);
+    k_reduce<<<nm + (extra >= 0 ? 1 : 0), 256, 0, s>>>(part, nblocks, nm, extra, out, arrived, done, seq);
     return hipGetLastError();
 }
 
@@ -539,24 +543,16 @@ __global__ void __launch_bounds__(256) k_warp_fused_yf(const F* __restrict__ f0,
     }
 }
 
+// The padded copy of a volume, zero borders included.
 template <typename R>
-__global__ void __launch_bounds__(256) k_pad(const R* __restrict__ vol, VoxGrid g, int px, int py,
-                                             R* __restrict__ pad)
+__global__ void __launch_bounds__(256) k_pad(const R* __restrict__ vol, VoxGrid g, R* __restrict__ pad)
 {
-    int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= g.nx || j >= g.ny) return;
-    size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-    pad[(size_t)(i + 1) + (size_t)px * ((size_t)(j + 1) + (size_t)py * (k + 1))] = vol[v];
-}
-
-template <typename R>
-__global__ void __launch_bounds__(256) k_unpad(const R* __restrict__ pad, VoxGrid g, int px,
-                                               int py, R* __restrict__ vol)
-{
-    int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
-    if (i >= g.nx || j >= g.ny) return;
-    size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-    vol[v] = pad[(size_t)(i + 1) + (size_t)px * ((size_t)(j + 1) + (size_t)py * (k + 1))];
+    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
+    if (i >= g.nx + 3 || j >= g.ny + 3) return;
+    const bool in = (unsigned)(i - 1) < (unsigned)g.nx && (unsigned)(j - 1) < (unsigned)g.ny &&
+                    (unsigned)(k - 1) < (unsigned)g.nz;
+    pad[(size_t)i + (size_t)(g.nx + 3) * ((size_t)j + (size_t)(g.ny + 3) * k)] =
+        in ? vol[(size_t)(i - 1) + (size_t)g.nx * ((size_t)(j - 1) + (size_t)g.ny * (k - 1))] : (R)0;
 }
 
 __global__ void __launch_bounds__(256) k_zero16(uint4* __restrict__ p, size_t n16)
@@ -1059,7 +1055,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
             }
         }
     }
-    if (A.ms.seg > 1) gather_segments<C>(smem, A.ms.seg, rpb, sid, acc, nsamp);
+    if (A.ms.seg > 1) gather_segments<C, 256>(smem, A.ms.seg, rpb, sid, acc, nsamp);
     if constexpr (H) {
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] *= A.ihs[c];   // exact: powers of two
@@ -1210,16 +1206,21 @@ __device__ __forceinline__ void load_to_lds(const char* src, float* dst)
 // read only those; the others stay zero); the sample loop accumulates only
 // these, so a 5-channel image stored in 6-channel cells (K = 4) does not pay
 // for the channel it does not use.
-template <int C, int KC = C>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<C>()))) k_march_lds(MarchArgs A)
+// NW: waves per block, the ray segments times the block's 64-ray tiles.
+// RAW (C = 1): the image is the caller's unpadded volume, and cells outside
+// it are staged as zeros, so a projection needs no padded copy.
+template <int C, int KC = C, int NW = 4, bool RAW = false>
+__global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<C>()))) k_march_lds(MarchArgs A)
 {
     static_assert(KC >= 1 && KC <= C, "used channels");
+    static_assert(!RAW || C == 1, "a raw image has one channel");
+    constexpr int T = 64 * NW;
     constexpr int CB = 4 * C;                    // bytes per cell
     constexpr int kStageBytes = stage_bytes<C>();
     using G = Stage<C, KC>;
     constexpr int BUF = G::buf;                  // cells per wave
     const RayGeom& g = A.g;
-    const int rpb = 256 / A.ms.seg;
+    const int rpb = T / A.ms.seg;
     const int rloc = threadIdx.x % rpb, sid = threadIdx.x / rpb;
     const int rows = rpb / A.ms.tile_u;
     int tu, tv;
@@ -1238,8 +1239,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
     rr.dq[0] = rr.dq[1] = rr.dq[2] = 0.0;
     // LDS: the block's ray set-ups, then the waves' staging buffers, then
     // the segments' partial sums (one after the other, so they share it)
-    constexpr int kStage = 4 * kStageBytes;
-    constexpr int kSeg = 256 * (C + 1) * 4;   // gather_segments
+    constexpr int kStage = NW * kStageBytes;
+    constexpr int kSeg = T * (C + 1) * 4;   // gather_segments
     constexpr int kRest = kSeg > 128 * (int)sizeof(RayRange) ? kSeg : 128 * (int)sizeof(RayRange);
     constexpr int kSmem = kStage > kRest ? kStage : kRest;
     __shared__ __align__(16) char smem[kSmem];
@@ -1269,7 +1270,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
         const float q0z = (float)(g.qs[2] + ta * rr.dq[2]) + 1.f;
         const float dqx = (float)(g.dt * rr.dq[0]), dqy = (float)(g.dt * rr.dq[1]),
                     dqz = (float)(g.dt * rr.dq[2]);
-        const int YS = A.ys, ZS = A.zs, YZ = A.ys + A.zs, PY = A.py;
+        const int YS = A.ys, ZS = A.zs, YZ = A.ys + A.zs, PY = RAW ? A.py - 3 : A.py;
         const char* vb = (const char*)A.vol;
         // The extremes over the wave's rays of a position's two coefficients
         // bound all its positions: every ray starts at the source, so per
@@ -1310,11 +1311,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
             const float ax = __builtin_amdgcn_fractf(qx), ay = __builtin_amdgcn_fractf(qy),
                         az = __builtin_amdgcn_fractf(qz);
             load(ix, iy, iz);
-            // each pair of weights from one product and one difference
-            const float bz = 1.f - az;
-            const float w10 = ay * bz, w00 = bz - w10, w11 = ay * az, w01 = az - w11;
-            const float w100 = ax * w00, w000 = w00 - w100, w110 = ax * w10, w010 = w10 - w110;
-            const float w101 = ax * w01, w001 = w01 - w101, w111 = ax * w11, w011 = w11 - w111;
+            // (one product a weight: forming each pair from a product and a
+            // difference saves two of the loop's ~66 instructions, but a
+            // solve carries the other rounding through its line searches)
+            const float bx = 1.f - ax, by = 1.f - ay, bz = 1.f - az;
+            const float w00 = by * bz, w10 = ay * bz, w01 = by * az, w11 = ay * az;
+            const float w000 = bx * w00, w100 = ax * w00, w010 = bx * w10, w110 = ax * w10;
+            const float w001 = bx * w01, w101 = ax * w01, w011 = bx * w11, w111 = ax * w11;
 #pragma unroll
             for (int c = 0; c < KC; ++c) {
                 float t = acc[c];
@@ -1394,25 +1397,40 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
                 const unsigned uYS = (unsigned)YS, uZS = (unsigned)ZS;
                 const unsigned a0 = (unsigned)sy * uYS + (unsigned)sz * uZS, a1 = a0 + uZS - (unsigned)dy * uYS;
                 const int zr = small_quot(r0, rdy);
+                // (raw: padded index 1 is the first voxel; a box inside the
+                // volume is copied like any other)
+                const unsigned shift = RAW ? (unsigned)CB + uYS + uZS : 0u;
+                const bool whole = !RAW || (lo0 >= 1 && lo1 >= 1 && lo2 >= 1 && lo0 + dx <= A.px - 2 &&
+                                            lo1 + dy <= A.py - 2 && lo2 + dz <= A.pz - 2);
                 for (int x0 = 0; x0 < dx; x0 += 64) {
                     const int lx = lane - (int)__umul24(r0, dx) + x0;
                     // rows left for this lane (none: its cell is beyond the row
                     // or belongs to the next pass)
                     const int left = (r0 < rpp && lx < dx) ? rows - r0 : 0;
                     int ly = r0 - (int)__umul24(zr, dy);
-                    unsigned goff = (unsigned)((lo0 + lx) * CB) + __umul24(__umul24(lo2 + zr, PY) + lo1 + ly, YS);
+                    unsigned goff = (unsigned)((lo0 + lx) * CB) + __umul24(__umul24(lo2 + zr, PY) + lo1 + ly, YS) - shift;
+                    int z = lo2 + zr;
                     auto next = [&] {
                         ly += sy;
                         const bool carry = ly >= dy;
                         ly -= carry ? dy : 0;
                         goff += carry ? a1 : a0;
+                        if (RAW) z += sz + (carry ? 1 : 0);
                     };
+                    const bool in_x = !RAW || (unsigned)(lo0 + lx - 1) < (unsigned)(A.px - 3);
                     // straight to LDS, without registers and without a wait
                     // before the last pass is issued; the lanes' cells are
                     // consecutive: r0 dx + lx = lane + x0 cells into the pass
                     int cell = x0;
                     for (int p = 0; p < rows; p += rpp) {
-                        if (left > p) {
+                        bool here = left > p;
+                        if (RAW && !whole) {
+                            const bool vox = in_x && (unsigned)(lo1 + ly - 1) < (unsigned)(A.py - 3) &&
+                                             (unsigned)(z - 1) < (unsigned)(A.pz - 3);
+                            if (here && !vox) st[cell + lane] = 0.f;
+                            here = here && vox;
+                        }
+                        if (here) {
                             const char* src = vb + goff;
 #pragma unroll
                             for (int h = 0; h < G::n16; ++h)
@@ -1473,6 +1491,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
             const float fe = (float)(g1 - na);
             for (float fm = (float)(g0 - na); fm <= fe; fm += 1.0f)
                 step(true, fm, P, [&](int ix, int iy, int iz) {
+                    if constexpr (RAW) {
+                        // taps outside the volume are zero; all eight loads
+                        // first, at clamped indices
+                        const int nx = A.px - 3, ny = A.py - 3, nz = A.pz - 3;
+                        float t[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const int x = min(max(ix - 1 + (e & 1), 0), nx - 1), y = min(max(iy - 1 + ((e >> 1) & 1), 0), ny - 1),
+                                      z = min(max(iz - 1 + (e >> 2), 0), nz - 1);
+                            t[e] = *(const float*)(vb + (unsigned)(x * CB) + __umul24(__umul24(z, ny) + y, YS));
+                        }
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            const bool vox = (unsigned)(ix - 1 + (e & 1)) < (unsigned)nx &&
+                                             (unsigned)(iy - 1 + ((e >> 1) & 1)) < (unsigned)ny &&
+                                             (unsigned)(iz - 1 + (e >> 2)) < (unsigned)nz;
+                            (e & 1 ? P[e >> 1].b[0] : P[e >> 1].a[0]) = vox ? t[e] : 0.f;
+                        }
+                        return;
+                    }
                     const int voff = ix * CB + (int)__umul24(__umul24(iz, PY) + iy, YS);
                     if (voff != last) {
                         last = voff;
@@ -1486,7 +1524,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(march_
     }
     if (A.ms.seg > 1) {
         __syncthreads();   // every wave is done with its staging buffer
-        gather_segments<C>(smem, A.ms.seg, rpb, sid, acc, nsamp);
+        gather_segments<C, T>(smem, A.ms.seg, rpb, sid, acc, nsamp);
     }
     const bool owner = valid && sid == 0;
     const float dt = (float)g.dt;
@@ -2180,7 +2218,7 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy)
     return r;
 }
 
-MarchShape choose_march_shape(const RayGeom& rg)
+MarchShape choose_march_shape(const RayGeom& rg, int staged_channels)
 {
     MarchShape ms;
     long rays = (long)rg.nu * rg.nv;
@@ -2189,6 +2227,14 @@ MarchShape choose_march_shape(const RayGeom& rg)
     // through the union of their sample ranges together (measured best on
     // both layouts)
     ms.seg = rays >= 8L * 1024 * 64 ? 1 : (rays >= 4L * 1024 * 64 ? 2 : 4);
+    // Fewer still: eight segments in blocks of eight waves, for one channel.
+    // With under three waves a SIMD a wave's chunks follow each other alone,
+    // so halving their number counts: 256x256x100 onto 128x96 pixels 78 -> 56
+    // us, onto 256x192 57 -> 49 us.  (Images of more channels keep four: a
+    // solve would carry the other grouping of a ray's sum through its line
+    // searches.  It gains 10 % at 128x96 pixels, and 24-byte cells lose 9 % at
+    // 256x192.)
+    if (staged_channels == 1 && rays < 65536) ms.seg = 8;
     ms.tile_u = 4;
     return ms;
 }
@@ -2200,7 +2246,7 @@ static int tiles_u_of(const RayGeom& rg, const MarchShape& ms)
 
 int march_blocks(const RayGeom& rg, const MarchShape& ms)
 {
-    int rpb = 256 / ms.seg, rows = rpb / ms.tile_u;
+    int rpb = ms.seg == 8 ? 64 : 256 / ms.seg, rows = rpb / ms.tile_u;
     return tiles_u_of(rg, ms) * ((rg.nv + rows - 1) / rows);
 }
 
@@ -2335,22 +2381,13 @@ hipError_t launch_warp_fused(pcr_dtype compute, pcr_dtype storage, pcr_dtype f0_
 hipError_t launch_pad(pcr_dtype compute, const PadLayout& L, const void* vol, void* padded,
                       hipStream_t s)
 {
+    if (L.C != 1 || L.half || L.yfast) return hipErrorInvalidValue;
     pcr_grid g{};
     g.n[0] = L.nx; g.n[1] = L.ny; g.n[2] = L.nz;
     g.spacing_mm[0] = g.spacing_mm[1] = g.spacing_mm[2] = 1.0;
+    const dim3 grid((L.px + 63) / 64, (L.py + 3) / 4, L.pz);
     PCR_DISPATCH_R(compute, R,
-        k_pad<R><<<vox_grid(g), dim3(64, 4), 0, s>>>((const R*)vol, vox(g), L.px, L.py, (R*)padded));
-    return hipGetLastError();
-}
-
-hipError_t launch_unpad(pcr_dtype compute, const PadLayout& L, const void* padded, void* vol,
-                        hipStream_t s)
-{
-    pcr_grid g{};
-    g.n[0] = L.nx; g.n[1] = L.ny; g.n[2] = L.nz;
-    g.spacing_mm[0] = g.spacing_mm[1] = g.spacing_mm[2] = 1.0;
-    PCR_DISPATCH_R(compute, R,
-        k_unpad<R><<<vox_grid(g), dim3(64, 4), 0, s>>>((const R*)padded, vox(g), L.px, L.py, (R*)vol));
+        k_pad<R><<<grid, dim3(64, 4), 0, s>>>((const R*)vol, vox(g), (R*)padded));
     return hipGetLastError();
 }
 
@@ -2375,8 +2412,8 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t s)
 template <typename R>
 static hipError_t march_r(const PadLayout& L, int kc, const RayGeom& rg, const MarchShape& ms,
                           const void* padded, const void* y, void* p_out, double* partials,
-                          double* moments, unsigned long long* done, unsigned long long seq,
-                          hipStream_t s)
+                          double* moments, unsigned* arrived, unsigned long long* done,
+                          unsigned long long seq, hipStream_t s)
 {
     int tiles_u = tiles_u_of(rg, ms);
     int blocks = march_blocks(rg, ms);
@@ -2397,7 +2434,7 @@ static hipError_t march_r(const PadLayout& L, int kc, const RayGeom& rg, const M
     if (moments) {
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        return run_reduce(partials, blocks, n_moments(kc), n_moments(L.C), moments, s, done, seq);
+        return run_reduce(partials, blocks, n_moments(kc), n_moments(L.C), moments, s, arrived, done, seq);
     }
     return hipGetLastError();
 }
@@ -2410,9 +2447,9 @@ bool march_f32_fits(const PadLayout& L)
 }
 
 static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const MarchShape& ms,
-                            const void* padded, const void* y, void* p_out, double* partials,
-                            double* moments, unsigned long long* done, unsigned long long seq,
-                            hipStream_t s)
+                            const void* padded, bool raw, const void* y, void* p_out, double* partials,
+                            double* moments, unsigned* arrived, unsigned long long* done,
+                            unsigned long long seq, hipStream_t s)
 {
     if (!march_f32_fits(L)) return hipErrorInvalidValue;
     MarchArgs A;
@@ -2424,8 +2461,9 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
     A.px = L.px;
     A.py = L.py;
     A.pz = L.pz;
-    A.ys = L.px * cb;
-    A.zs = L.px * L.py * cb;
+    // (raw: the caller's volume, without the padding)
+    A.ys = (raw ? L.px - 3 : L.px) * cb;
+    A.zs = A.ys * (raw ? L.py - 3 : L.py);
     for (int c = 0; c < 8; ++c) A.ihs[c] = 1.0f / L.hs[c];
     for (int a = 0; a < 3; ++a) A.fn1[a] = (float)(rg.lim[a] + 1.0);
     A.kc = kc;
@@ -2434,7 +2472,7 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
     A.partials = moments ? partials : nullptr;
     A.moments = moments;
     int blocks = march_blocks(rg, ms);
-    if (L.half && L.C == 1) return hipErrorInvalidValue;
+    if (L.half && (L.C == 1 || ms.seg > 4)) return hipErrorInvalidValue;
     if (L.half) {
         switch (L.C) {
         case 2: k_march_f32<2, true><<<blocks, 256, 0, s>>>(A); break;
@@ -2445,37 +2483,79 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
     } else {
         // every FP32 cell size stages through LDS (8-byte cells too: 11-18 %
         // faster than the gather through the L1 at paper scale, K = 1)
+        if (ms.seg > 4 && L.C != 1) return hipErrorInvalidValue;
+#define PCR_ML(...) k_march_lds<__VA_ARGS__><<<blocks, 256, 0, s>>>(A)
         switch (L.C) {
-        case 1: k_march_lds<1><<<blocks, 256, 0, s>>>(A); break;
-        case 2: k_march_lds<2><<<blocks, 256, 0, s>>>(A); break;
-        case 4: k_march_lds<4><<<blocks, 256, 0, s>>>(A); break;
+        case 1:
+            if (raw)
+                ms.seg == 8 ? k_march_lds<1, 1, 8, true><<<blocks, 512, 0, s>>>(A)
+                            : k_march_lds<1, 1, 4, true><<<blocks, 256, 0, s>>>(A);
+            else
+                ms.seg == 8 ? k_march_lds<1, 1, 8><<<blocks, 512, 0, s>>>(A) : PCR_ML(1, 1);
+            break;
+        case 2: PCR_ML(2, 2); break;
+        case 4: PCR_ML(4, 4); break;
         case 6:
             // K = 4 sums 5 of the 6 channels.  (Summing only the channels in
             // use pays where the unused ones drop whole loads; 12-byte LDS
             // reads, as for K = 2 in 4-channel cells, were slower than
             // summing the zero channel: 183.6 against 145.6 us at K = 2.)
-            if (kc == 5) k_march_lds<6, 5><<<blocks, 256, 0, s>>>(A);
-            else k_march_lds<6><<<blocks, 256, 0, s>>>(A);
+            if (kc == 5) PCR_ML(6, 5);
+            else PCR_ML(6, 6);
             break;
-        case 8: k_march_lds<8><<<blocks, 256, 0, s>>>(A); break;
+        case 8: PCR_ML(8, 8); break;
         default: return hipErrorInvalidValue;
         }
+#undef PCR_ML
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !moments) return e;
-    return run_reduce(partials, blocks, n_moments(kc), n_moments(L.C), moments, s, done, seq);
+    return run_reduce(partials, blocks, n_moments(kc), n_moments(L.C), moments, s, arrived, done, seq);
 }
 
 hipError_t launch_march(pcr_dtype compute, const PadLayout& L, int kc, const RayGeom& rg,
                         const MarchShape& ms, const void* padded, const void* y, void* p_out,
-                        double* partials, double* moments, unsigned long long* done,
-                        unsigned long long seq, hipStream_t s)
+                        double* partials, double* moments, unsigned* arrived,
+                        unsigned long long* done, unsigned long long seq, hipStream_t s)
 {
+    if (moments && done && !arrived) return hipErrorInvalidValue;
     if (compute == PCR_F32)
-        return march_f32(L, kc, rg, ms, padded, y, p_out, partials, moments, done, seq, s);
+        return march_f32(L, kc, rg, ms, padded, false, y, p_out, partials, moments, arrived, done, seq, s);
     if (compute == PCR_F64)
-        return march_r<double>(L, kc, rg, ms, padded, y, p_out, partials, moments, done, seq, s);
+        return march_r<double>(L, kc, rg, ms, padded, y, p_out, partials, moments, arrived, done, seq, s);
     return hipErrorInvalidValue;
+}
+
+bool project_unpadded(pcr_dtype compute, const RayGeom& rg)
+{
+    // Without the copy a projection saves its pass over the volume (15-25 us
+    // at paper scale: 137 -> 126 us there, 64^3 onto 128x96 13.7 -> 10.5 us),
+    // but where the rays of a tile spread too far to be staged, the gather
+    // through the L1 pays for checking every tap against the volume's edges
+    // (256x256x100 onto 40x30: 116 -> 129 us).  The line: whether the cells of
+    // four samples of a 4 x 16 tile, at the isocentre's magnification, fit
+    // a wave's staging buffer.
+    if (compute != PCR_F32) return false;
+    double n[3], q = 0.0, d = 0.0;
+    for (int a = 0; a < 3; ++a) {
+        n[a] = (rg.qc[a] - rg.qs[a]) * rg.sp[a];
+        q += n[a] * n[a];
+        // depth of the grid's centre along the central ray
+        d += (0.5 * (rg.lim[a] - 1.0) - rg.qs[a]) * rg.sp[a] * n[a];
+    }
+    const double mag = q > 0.0 ? d / q : 1.0, len = std::sqrt(q);
+    double cells = 1.0;
+    for (int a = 0; a < 3; ++a)
+        cells *= mag * (3.0 * rg.du * std::fabs(rg.eu[a]) + 15.0 * rg.dv * std::fabs(rg.ev[a])) +
+                 3.0 * rg.dt * std::fabs(n[a]) / (len * rg.sp[a]) + 2.0;
+    return cells <= Stage<1, 1>::buf;
+}
+
+hipError_t launch_project_f32(const PadLayout& L, const RayGeom& rg, const MarchShape& ms, const void* vol,
+                              void* p_out, hipStream_t s)
+{
+    if (L.C != 1 || L.half || L.yfast) return hipErrorInvalidValue;
+    return march_f32(L, 1, rg, ms, vol, true, nullptr, p_out, nullptr, nullptr, nullptr, nullptr, 0, s);
 }
 
 hipError_t launch_reduce(const double* partials, int nblocks, int nm, double* out, hipStream_t s)

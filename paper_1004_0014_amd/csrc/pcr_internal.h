@@ -82,9 +82,12 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy = false
 // Launch shape of the ray-march kernels.
 struct MarchShape {
     int tile_u;          // pixels along u covered by one wave (64 / tile_u rows)
-    int seg;             // ray segments (threads) per ray: 1, 2 or 4
+    int seg;             // ray segments (threads) per ray: 1, 2 or 4, or 8 (blocks of
+                         // 512 threads; staged march of one channel only)
 };
-MarchShape choose_march_shape(const RayGeom& rg);
+// staged_channels: channels per cell of the FP32 march through LDS, 0 for the
+// other marches
+MarchShape choose_march_shape(const RayGeom& rg, int staged_channels);
 
 // Moments returned by a ray march over channels (f, h_1..h_K):
 //   0 sum y, 1 sum y^2, 2 sum p, 3 sum y p, 4 sum p^2,
@@ -118,21 +121,27 @@ hipError_t launch_warp_fused(pcr_dtype compute, pcr_dtype storage, pcr_dtype f0_
                              const pcr_grid& g, const PadLayout& L, int K, bool tangent,
                              const void* f0, const void* mean, const void* U,
                              const double* w_eff, const int* box, void* padded, hipStream_t s);
+// Padded copy of a volume, zero borders included (one channel, x-fastest).
 hipError_t launch_pad(pcr_dtype compute, const PadLayout& L, const void* vol, void* padded,
                       hipStream_t s);
-hipError_t launch_unpad(pcr_dtype compute, const PadLayout& L, const void* padded, void* vol,
-                        hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 // Ray march over kc used channels of a padded image; writes p (may be null)
 // and, when moments != null, the detector moments (y required then; uses
 // `partials`, room for march_blocks x kMaxMoments doubles).  With done !=
 // null the final sum then stores `seq` into *done (system scope, after the
 // moments are visible there): moments and done may point into mapped host
-// memory.
+// memory.  `arrived` is a device word, zero before the first launch, that
+// only launches on one stream share.
 hipError_t launch_march(pcr_dtype compute, const PadLayout& L, int kc, const RayGeom& rg,
                         const MarchShape& ms, const void* padded, const void* y, void* p_out,
-                        double* partials, double* moments, unsigned long long* done,
-                        unsigned long long seq, hipStream_t s);
+                        double* partials, double* moments, unsigned* arrived,
+                        unsigned long long* done, unsigned long long seq, hipStream_t s);
+// Whether a projection is better off reading the volume itself than a padded
+// copy of it (FP32 staged march), and that projection (L: the layout the
+// padded copy would have).
+bool project_unpadded(pcr_dtype compute, const RayGeom& rg);
+hipError_t launch_project_f32(const PadLayout& L, const RayGeom& rg, const MarchShape& ms, const void* vol,
+                              void* p_out, hipStream_t s);
 // Fixed-order final sum of per-block partials: out[m] for m < nm.
 // Per slice z of f0, bounds of its nonzero voxels (i, j): sl[8 z ..] =
 // {min i, max i, min j, max j, min i+j, max i+j, min i-j, max i-j}; the

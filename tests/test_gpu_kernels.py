@@ -25,6 +25,11 @@ def _lib():
     ((5, 4, 90), (20.0, 20.0, 1.0), 19, 65, 1.5, 0.5, 200.0),   # boxes of short rows, many slices
     ((40, 40, 40), (2.0, 2.0, 2.0), 8, 6, 40.0, 1.0, 30.0),     # no box fits: the L1 gather
     ((40, 40, 40), (2.0, 2.0, 2.0), 67, 50, 2.0, 1.0, 30.0),    # ragged detector tiles
+    ((40, 40, 40), (2.0, 2.0, 2.0), 14, 40, 5.0, 1.0, 30.0),    # boxes near the buffer's size, on
+    ((40, 40, 40), (2.0, 2.0, 2.0), 14, 40, 6.5, 1.0, 30.0),    # either side of the padded copy's
+    ((40, 40, 40), (2.0, 2.0, 2.0), 14, 40, 8.0, 1.0, 30.0),    # rule; some tiles gather
+    ((1, 7, 9), (2.0, 2.0, 2.0), 30, 30, 0.6, 1.0, 75.0),       # one voxel along the fastest axis
+    ((64, 64, 12), (2.0, 2.0, 3.0), 512, 130, 0.5, 1.0, 10.0),  # four segments instead of eight
 ])
 def test_staged_march_box_shapes(n, sp, nu, nv, du, step, ang):
     """The staged march's boxes of cells in all their shapes; FP32 sums of a
