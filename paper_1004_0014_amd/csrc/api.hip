@@ -582,10 +582,8 @@ pcr_status Evaluator::enqueue_eval(const double* w)
     return PCR_OK;
 }
 
-pcr_status Evaluator::wait_published()
+pcr_status wait_published(const unsigned long long* done, unsigned long long want, hipStream_t s)
 {
-    const unsigned long long* done = (const unsigned long long*)(sc->host.p + kDoneSlot);
-    const unsigned long long want = sc->seq;
     for (unsigned long n = 1;; ++n) {
         if (__atomic_load_n(done, __ATOMIC_ACQUIRE) == want) return PCR_OK;
         if ((n & 4095) == 0) {
@@ -594,12 +592,17 @@ pcr_status Evaluator::wait_published()
             const hipError_t q = hipStreamQuery(s);
             if (q == hipSuccess) {
                 if (__atomic_load_n(done, __ATOMIC_ACQUIRE) == want) return PCR_OK;
-                return fail(PCR_EDEVICE, "evaluation finished without publishing its moments");
+                return fail(PCR_EDEVICE, "the kernels finished without publishing their sums");
             }
             if (q != hipErrorNotReady) return fail(PCR_EDEVICE, "evaluation: %s", hipGetErrorString(q));
         }
         __builtin_ia32_pause();
     }
+}
+
+pcr_status Evaluator::wait_published()
+{
+    return pcr::wait_published((const unsigned long long*)(sc->host.p + kDoneSlot), sc->seq, s);
 }
 
 void Evaluator::collect(Moments& out) const

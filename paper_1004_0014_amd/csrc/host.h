@@ -102,6 +102,10 @@ struct HostBuf {
     void release();
 };
 
+// Spins until a kernel on `s` has stored `want` into the mapped host word
+// *done (checking the stream for errors now and then).
+pcr_status wait_published(const unsigned long long* done, unsigned long long want, hipStream_t s);
+
 // Host staging of an evaluation's results: the moments and the samples
 // count, then (at kDoneSlot, as an unsigned 64-bit word) the sequence number
 // the final-sum kernel stores once they are written.

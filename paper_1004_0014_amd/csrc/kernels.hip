@@ -1725,7 +1725,9 @@ __device__ __forceinline__ double saturate(double x) { return fmax(x, 0.0); }
 // rays (six blocks) 752 / 630 / 710 us; 8 x 4 or 4 x 8 columns with 8 lanes
 // each 750-1570 us.
 constexpr int kBpTileU = 8, kBpTileV = 32;   // staged rays: one per thread
-template <typename R>
+// CB x CB columns a brick (along the other in-plane axis and z), the block's
+// 256 threads split evenly over them.
+template <typename R, int CB>
 __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* __restrict__ resid,
                                                              const R* __restrict__ p,
                                                              const R* __restrict__ y,
@@ -1760,8 +1762,9 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     const int AX = A.ax, BX = 1 - A.ax;           // column axis and the other in-plane axis
     // a wave holds 4 columns x 16 lanes: consecutive lanes take consecutive
     // rays of one column, so their record loads hit distinct banks
-    const int col = t >> 4, lane = t & 15;        // column (lb, lz) and ray lane
-    const int lb = col & 3, lz = col >> 2;
+    constexpr int LPC = 256 / (CB * CB);
+    const int col = t / LPC, lane = t % LPC;        // column (lb, lz) and ray lane
+    const int lb = col % CB, lz = col / CB;
     for (int e = t; e < 256 * 20; e += 256) s_acc[e] = (R)0;
     R* acc = s_acc + t;
     if (t == 0) {
@@ -1858,21 +1861,21 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
             }
             __syncthreads();
             // rays of this tile inside the column's footprint, split over the
-            // column's 16 lanes
+            // column's lanes
             const int ua = max(ru0, tu0), ub = min(ru1, tu0 + TU - 1);
             const int va = max(rv0, tv0), vb = min(rv1, tv0 + TV - 1);
             const int wu = ub - ua + 1, nr = (ub >= ua && vb >= va) ? wu * (vb - va + 1) : 0;
             // ray i of the clipped box (row-major) is (i % wu, i / wu); the
-            // lane steps i by 16, i.e. (16 % wu, 16 / wu) with one carry
+            // lane steps i by LPC, i.e. (LPC % wu, LPC / wu) with one carry
             const int kb = (va - tv0) * TU + (ua - tu0);
             int ou = 0, ov = 0, su = 0, sv = 0;
             if (nr > 0) {
                 ou = lane % wu;
                 ov = lane / wu;
-                su = 16 % wu;
-                sv = 16 / wu;
+                su = LPC % wu;
+                sv = LPC / wu;
             }
-            for (int i = lane; i < nr; i += 16) {
+            for (int i = lane; i < nr; i += LPC) {
                 const int k = kb + ov * TU + ou;
                 ou += su;
                 ov += sv;
@@ -1922,15 +1925,21 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
             __syncthreads();
         }
     }
+    // voxel (column c, position j along A): the sum over the column's lanes,
+    // in an order rotated by j so that the lanes of a wave read different
+    // banks; with few columns several threads share a voxel's sum
     {
-        const int c = t >> 4, j = t & 15;
+        constexpr int NP = 256 / (CB * CB * 16), per = LPC / NP;
+        const int o = t / NP, part = t % NP, c = o >> 4, j = o & 15;
         R v = (R)0;
-        for (int l = 0; l < 16; ++l) v += s_acc[(2 + j) * 256 + c * 16 + ((l + j) & 15)];
+        for (int l = 0; l < per; ++l) v += s_acc[(2 + j) * 256 + c * LPC + part * per + ((l + j) & (per - 1))];
+#pragma unroll
+        for (int x = 1; x < NP; x <<= 1) v += __shfl_xor(v, x);
         int vx[3];
         vx[AX] = b0[AX] + j;
-        vx[BX] = b0[BX] + (c & 3);
-        vx[2] = b0[2] + (c >> 2);
-        if (vx[0] < A.nx && vx[1] < A.ny && vx[2] < A.nz)
+        vx[BX] = b0[BX] + c % CB;
+        vx[2] = b0[2] + c / CB;
+        if (part == 0 && vx[0] < A.nx && vx[1] < A.ny && vx[2] < A.nz)
             out[(size_t)vx[0] + (size_t)A.nx * ((size_t)vx[1] + (size_t)A.ny * vx[2])] = v;
     }
 }
@@ -2563,6 +2572,13 @@ hipError_t launch_reduce(const double* partials, int nblocks, int nm, double* ou
     return run_reduce(partials, nblocks, nm, -1, out, s);
 }
 
+hipError_t launch_reduce_publish(const double* partials, int nblocks, int nm, double* out, unsigned* arrived,
+                                 unsigned long long* done, unsigned long long seq, hipStream_t s)
+{
+    if (!arrived || !done) return hipErrorInvalidValue;
+    return run_reduce(partials, nblocks, nm, -1, out, s, arrived, done, seq);
+}
+
 hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeom& rg,
                               const void* resid, const void* p, const void* y, double a, double b,
                               double scale, void* out, hipStream_t s)
@@ -2605,24 +2621,41 @@ hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeo
     A.F.inv_dv = (float)(1.0 / rg.dv);
     A.F.nu = rg.nu;
     A.F.nv = rg.nv;
-    // bricks elongated along the rays' dominant in-plane axis
+    // bricks of 16 voxels along the rays' dominant in-plane axis by cb x cb
     const double rx = std::fabs(rg.qc[0] - rg.qs[0]) * rg.sp[0], ry = std::fabs(rg.qc[1] - rg.qs[1]) * rg.sp[1];
-    if (ry >= rx) { A.ax = 1; A.bx = 4; A.by = 16; } else { A.ax = 0; A.bx = 16; A.by = 4; }
-    A.bz = 4;
+    A.ax = ry >= rx ? 1 : 0;
     A.nx = g.n[0];
     A.ny = g.n[1];
     A.nz = g.n[2];
-    A.nbx = (A.nx + A.bx - 1) / A.bx;
-    A.nby = (A.ny + A.by - 1) / A.by;
-    const int nbz = (A.nz + A.bz - 1) / A.bz;
     A.a = a;
     A.b = b;
     A.scale = scale;
-    const long blocks = (long)A.nbx * A.nby * nbz;
+    auto bricks = [&](int cb) {
+        A.bx = A.ax ? cb : 16;
+        A.by = A.ax ? 16 : cb;
+        A.bz = cb;
+        A.nbx = (A.nx + A.bx - 1) / A.bx;
+        A.nby = (A.ny + A.by - 1) / A.by;
+        return (long)A.nbx * A.nby * ((A.nz + A.bz - 1) / A.bz);
+    };
+    long blocks = bricks(4);
     if (blocks <= 0 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    PCR_DISPATCH_R(compute, R,
-        k_backproject_columns<R><<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p,
-                                                                (const R*)y, (R*)out));
+    if (blocks < 1024) {
+        // fewer than the chip holds at once (five per CU): 2 x 2 columns make
+        // four times the blocks, each column with 64 lanes for its rays
+        // (51x57x41 voxels, 623x462 pixels: 4.4 -> 0.54 ms; 48x48x32, 128x96:
+        // 38 -> 24 us; 80x80x40, 256x192: 92 -> 80 us).  At 1024 blocks (64^3)
+        // the two are equal; beyond, the rays staged once per brick count: 4096
+        // blocks 99 against 165 us.
+        blocks = bricks(2);
+        PCR_DISPATCH_R(compute, R,
+            k_backproject_columns<R, 2><<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p,
+                                                                       (const R*)y, (R*)out));
+    } else {
+        PCR_DISPATCH_R(compute, R,
+            k_backproject_columns<R, 4><<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p,
+                                                                       (const R*)y, (R*)out));
+    }
     return hipGetLastError();
 }
 

@@ -154,6 +154,9 @@ hipError_t launch_absmax_rows(pcr_dtype dt, const void* a, size_t n, int rows, f
 // out[m] = sum over blocks b of partials[m * nblocks + b] (slot-major), m < nm;
 // fixed order.
 hipError_t launch_reduce(const double* partials, int nblocks, int nm, double* out, hipStream_t s);
+// The same, then `seq` stored into *done (as by launch_march).
+hipError_t launch_reduce_publish(const double* partials, int nblocks, int nm, double* out, unsigned* arrived,
+                                 unsigned long long* done, unsigned long long seq, hipStream_t s);
 // Backprojection out = P^T r (unpadded [N], fully overwritten) with r = resid
 // (when resid != null) else scale * (p - a y - b); x-fastest geometry.
 hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeom& rg,
