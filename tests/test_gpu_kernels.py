@@ -67,3 +67,39 @@ def test_voxel_passes_at_row_ends(n, K, storage):
     adj = L.warp_adjoint(g, x, v.to(DEV)).cpu().numpy()
     refa = oracle.warp_adjoint(g, x64, v.double().numpy())
     assert np.linalg.norm(adj - refa) <= 1e-5 * np.linalg.norm(v.numpy())
+
+
+@pytest.mark.parametrize("n,nu,nv,du,ang", [
+    ((40, 33, 21), 61, 47, 0.9, 20.0),      # 2 x 2 columns: few bricks, fine detector
+    ((33, 40, 21), 61, 47, 0.9, 110.0),
+    ((3, 2, 1), 40, 40, 0.2, 45.0),         # less than a brick
+    ((130, 90, 61), 40, 33, 5.0, 70.0),     # 4 x 4 columns
+])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_backprojection_brick_shapes(n, nu, nv, du, ang, dtype):
+    """Both brick shapes with partial bricks on every axis; a voxel sums a few
+    hundred weighted samples: the backprojection parity bounds."""
+    L = _lib()
+    g = S.Grid(n, (2.0, 2.5, 3.0))
+    G = S.Geom(math.radians(ang), nu, nv, du, du, 1.0, off_u=0.3)
+    r_t, r = rounded(S.seeded(4, (nv, nu)), dtype)
+    bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
+    assert rel_l2(bp, oracle.backproject(g, G, r)) <= (1e-5 if dtype == torch.float32 else 1e-12)
+
+
+@pytest.mark.parametrize("n,J,K", [((3, 1, 1), 3, 1), ((11, 7, 5), 2, 1), ((33, 21, 13), 16, 8), ((64, 40, 31), 10, 3)])
+@pytest.mark.parametrize("turn", [1.0, -1.0])
+def test_pca_chunks_and_signs(n, J, K, turn):
+    """PCA of random fields: chunks with remainders, fewer values than the sign
+    guess samples, every J class; negated inputs give the same signs.  FP32
+    sums of J products against the FP64 oracle: 1e-5."""
+    L = _lib()
+    g = S.Grid(n, (2.0, 2.0, 2.0))
+    rng = np.random.default_rng(11)
+    d = (turn * rng.standard_normal((J, 3) + g.shape) * (1.0 + np.arange(J))[:, None, None, None, None]).astype(np.float32)
+    mean, U, sing, wt = L.pca_train(g, torch.from_numpy(d).to(DEV), K)
+    mo, Uo, so, wo = oracle.pca(d.astype(np.float64), K)
+    assert rel_l2(mean.cpu().numpy(), mo) <= 1e-5
+    assert rel_l2(U.cpu().numpy(), Uo) <= 1e-5
+    np.testing.assert_allclose(sing, so, rtol=1e-6)
+    np.testing.assert_allclose(wt, wo, rtol=1e-5, atol=1e-5 * np.abs(wo).max())
