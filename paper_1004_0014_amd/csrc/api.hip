@@ -197,7 +197,7 @@ pcr_status HostBuf::ensure(size_t need)
     if (p) HIP_TRY(hipHostFree(p));
     p = d = nullptr;
     n = 0;
-    HIP_TRY(hipHostMalloc((void**)&p, need * sizeof(double), hipHostMallocCoherent | hipHostMallocMapped));
+    HIP_TRY(hipHostMalloc((void**)&p, need * sizeof(double), hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable));
     std::memset(p, 0, need * sizeof(double));
     hipError_t e = hipHostGetDevicePointer((void**)&d, p, 0);
     if (e != hipSuccess) {
@@ -309,7 +309,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     y = y_;
     mode = mode_;
     rg = make_ray_geom(*grid, G);
-    ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
+    ms = choose_march_shape(rg, false);
     M = G.nu * G.nv;
     blocks = march_blocks(rg, ms);
     const bool yfast = prefer_yfast(G);
@@ -326,7 +326,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     }
     sc->L1 = make_pad(*grid, 1);
     rgc = make_ray_geom(*grid, G, yfast);
-    msc = choose_march_shape(rgc, compute == PCR_F32 && !sc->Lc.half ? sc->Lc.C : 0);
+    msc = choose_march_shape(rgc, false);
     blocksc = march_blocks(rgc, msc);
     const int dev = sc->device;
     if (mode == PCR_GRAD_FUSED) {
@@ -639,11 +639,11 @@ pcr_status Evaluator::grad_adjoint(const double* w, double a, double b, double* 
     }
     {
         PROF(REDUCE, s);
-        HIP_TRY(launch_reduce((const double*)sc->partials.p, contract_blocks(*grid), K,
-                              (double*)sc->moments.p, s));
+        HIP_TRY(launch_reduce_publish((const double*)sc->partials.p, contract_blocks(*grid), K, sc->host.d,
+                                      (unsigned*)((double*)sc->moments.p + kMaxMoments),
+                                      (unsigned long long*)(sc->host.d + kDoneSlot), ++sc->seq, s));
     }
-    HIP_TRY(hipMemcpyAsync(sc->host.p, sc->moments.p, K * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    PCR_TRY(wait_published());
     for (int k = 0; k < K; ++k) grad[k] = sc->host.p[k];
     return PCR_OK;
 }
@@ -653,12 +653,12 @@ pcr_status Evaluator::grad_adjoint(const double* w, double a, double b, double* 
 // Per-thread scratch of the stateless entry points.
 namespace {
 struct TlsScratch {
-    DevBuf pad, small;
-    HostBuf host;
+    DevBuf pad;
+    HostBuf host;   // up to 8 results, then the sequence number of published ones
+    unsigned long long seq = 0;
     ~TlsScratch()
     {
         pad.release();
-        small.release();
         host.release();
     }
 };
@@ -828,7 +828,7 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     hipStream_t s = (hipStream_t)stream;
     const PadLayout L = make_pad(*grid, 1);
     const RayGeom rg = make_ray_geom(*grid, *geom);
-    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
+    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32);
     if (project_unpadded(compute, rg)) {
         PROF(MARCH, s);
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
@@ -865,7 +865,7 @@ pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geo
                     grid->n[0], grid->n[1], grid->n[2], bytes, (size_t)PCR_NOALLOC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
     const RayGeom rg = make_ray_geom(*grid, *geom);
-    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32 ? 1 : 0);
+    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32);
     if (project_unpadded(compute, rg)) {
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;
@@ -956,19 +956,16 @@ pcr_status pcr_localize_tumor(const pcr_grid* grid, const pcr_model* model, cons
     if (!p_out_mm) return fail(PCR_EINVAL, "p_out_mm is NULL");
     if (!(tol_mm > 0) || max_iter < 1) return fail(PCR_EINVAL, "need tol_mm > 0 and max_iter >= 1");
     hipStream_t s = (hipStream_t)stream;
-    int dev;
-    PCR_TRY(current_device(&dev));
-    PCR_TRY(tls.small.ensure(8 * sizeof(double), dev, s));
-    PCR_TRY(tls.host.ensure(8));
+    PCR_TRY(tls.host.ensure(9));
     double w_eff[8];
     effective_w(*model, w_host, w_eff);
+    const unsigned long long seq = ++tls.seq;
     {
         PROF(LOCALIZE, s);
         HIP_TRY(launch_localize(model->storage, *grid, model->K, model->mean, model->U, w_eff, p_ref_mm,
-                                tol_mm, max_iter, (double*)tls.small.p, s));
+                                tol_mm, max_iter, tls.host.d, (unsigned long long*)(tls.host.d + 8), seq, s));
     }
-    HIP_TRY(hipMemcpyAsync(tls.host.p, tls.small.p, 5 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    PCR_TRY(wait_published((const unsigned long long*)(tls.host.p + 8), seq, s));
     for (int a = 0; a < 3; ++a) p_out_mm[a] = tls.host.p[a];
     if (iters) *iters = (int32_t)tls.host.p[3];
     if (tls.host.p[4] != 1.0) return fail(PCR_EDIVERGE, "fixed point did not converge in %d iterations", max_iter);

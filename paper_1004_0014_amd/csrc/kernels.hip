@@ -126,7 +126,7 @@ __device__ __forceinline__ void wave_sums(double (&v)[N])
 // the block's other waves wait for.)
 template <int NM>
 __device__ __forceinline__ void block_sum_store(double (&m)[NM], int nm, double* dst, int stride,
-                                                int nw = 4)
+                                                int nw = 4, bool through = false)
 {
     constexpr int N = (NM + 3) / 4 * 4, Q = N / 4;
     __shared__ double red[4][N];
@@ -145,7 +145,10 @@ __device__ __forceinline__ void block_sum_store(double (&m)[NM], int nm, double*
     if ((int)threadIdx.x < nm) {
         double s = red[0][threadIdx.x];
         for (int w2 = 1; w2 < nw; ++w2) s += red[w2][threadIdx.x];
-        dst[(size_t)threadIdx.x * stride] = s;
+        // (through: past this XCD's L2, for a block on another one)
+        if (through)
+            __hip_atomic_store(&dst[(size_t)threadIdx.x * stride], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else dst[(size_t)threadIdx.x * stride] = s;
     }
 }
 
@@ -221,6 +224,60 @@ static hipError_t run_reduce(const double* part, int nblocks, int nm, int extra,
 {
     k_reduce<<<nm + (extra >= 0 ? 1 : 0), 256, 0, s>>>(part, nblocks, nm, extra, out, arrived, done, seq);
     return hipGetLastError();
+}
+
+// The same sums at the end of the kernel that makes the partials, by its last
+// block to arrive (256 threads; every block calls this after block_sum_store
+// with `through`): where the blocks are few, a launch and the gap before it
+// cost more than one block reading all partials.  The partials were stored
+// past the L2s and each block waits for its own to complete before it counts
+// itself, so no cache is written back (a device-wide fence per block made
+// this slower than a second launch).  Only for NM + 1 <= 64 slots.
+constexpr int kFusedSumBlocks = 512;
+template <int NM>
+__device__ __forceinline__ void last_block_sums(const double* part, int nm, int extra, double* out, unsigned* arrived,
+                                                unsigned long long* done, unsigned long long seq)
+{
+    static_assert(NM + 1 <= 64, "slots stored by the first wave");
+    __shared__ int last;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nb = gridDim.x;
+    if (wv == 0) {
+        __builtin_amdgcn_s_waitcnt(0);   // this wave's partials are stored
+        asm volatile("" ::: "memory");
+        if (lane == 0) last = atomicInc(arrived, (unsigned)nb - 1) == (unsigned)nb - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    constexpr int NO = (NM + 1 + 3) / 4;   // outputs a wave: wv, wv + 4, ...
+    constexpr int QN = NM <= 14 ? 4 : 2;   // reads in flight for each, as registers allow
+    const int nout = nm + 1;
+    double s[NO];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) s[i] = 0.0;
+    for (int b0 = lane; b0 < nb; b0 += 64 * QN) {
+        double v[NO][QN];
+#pragma unroll
+        for (int i = 0; i < NO; ++i) {
+            const int o = min(wv + 4 * i, nout - 1);
+            const double* r = part + (size_t)(o < nm ? o : extra) * nb;
+#pragma unroll
+            for (int q = 0; q < QN; ++q)
+                v[i][q] = __hip_atomic_load(&r[min(b0 + 64 * q, nb - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+        for (int i = 0; i < NO; ++i)
+#pragma unroll
+            for (int q = 0; q < QN; ++q) s[i] += b0 + 64 * q < nb ? v[i][q] : 0.0;
+    }
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        const double t = wave_sum(s[i]);
+        if (lane == 0 && wv + 4 * i < nout)
+            __hip_atomic_store(&out[wv + 4 * i], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------ compose ----
@@ -925,7 +982,11 @@ struct MarchArgs {
     const float* y;        // measured projection (moments) or null
     float* p_out;          // projection out or null
     double* partials;      // [NM][blocks] (slot-major) or null
-    double* moments;       // final moments (last block) or null
+    // the final moments and their publication, where the last block sums them
+    double* moments;
+    unsigned* arrived;
+    unsigned long long* done;
+    unsigned long long seq;
     float ihs[8];          // FP16 cells: 1 / channel scale
 };
 
@@ -1209,7 +1270,9 @@ __device__ __forceinline__ void load_to_lds(const char* src, float* dst)
 // NW: waves per block, the ray segments times the block's 64-ray tiles.
 // RAW (C = 1): the image is the caller's unpadded volume, and cells outside
 // it are staged as zeros, so a projection needs no padded copy.
-template <int C, int KC = C, int NW = 4, bool RAW = false>
+// SUM: the last block forms the final moments (few blocks; a branch in one
+// kernel for both cost the large launches 0.7 %).
+template <int C, int KC = C, int NW = 4, bool RAW = false, bool SUM = false>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<C>()))) k_march_lds(MarchArgs A)
 {
     static_assert(KC >= 1 && KC <= C, "used channels");
@@ -1553,7 +1616,9 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ma
                 }
             }
         }
-        block_sum_store<NM + 1>(mo, NM + 1, A.partials + blockIdx.x, (int)gridDim.x, rpb / 64);
+        block_sum_store<NM + 1>(mo, NM + 1, A.partials + blockIdx.x, (int)gridDim.x, rpb / 64, SUM);
+        if constexpr (SUM)
+            last_block_sums<NM>(A.partials, 5 + 3 * (A.kc - 1), NM, A.moments, A.arrived, A.done, A.seq);
     }
 }
 
@@ -2078,7 +2143,8 @@ __global__ void __launch_bounds__(64) k_localize(const S* __restrict__ mean,
                                                  Chan<double, 8> w, VoxGrid g, double pr0,
                                                  double pr1, double pr2, double org0, double org1,
                                                  double org2, double tol, int max_iter,
-                                                 double* __restrict__ out)
+                                                 double* out, unsigned long long* done,
+                                                 unsigned long long seq)
 {
     const int t = threadIdx.x;
     const size_t N = (size_t)g.nx * g.ny * g.nz;
@@ -2133,11 +2199,12 @@ __global__ void __launch_bounds__(64) k_localize(const S* __restrict__ mean,
         }
     }
     if (t == 0) {
-        out[0] = p[0];
-        out[1] = p[1];
-        out[2] = p[2];
-        out[3] = (double)(it > max_iter ? max_iter : it);
-        out[4] = (double)conv;
+        // straight to the host's mapped memory, then the sequence number
+        const double r[5] = {p[0], p[1], p[2], (double)(it > max_iter ? max_iter : it), (double)conv};
+#pragma unroll
+        for (int i = 0; i < 5; ++i) __hip_atomic_store(&out[i], r[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __builtin_amdgcn_s_waitcnt(0);
+        __hip_atomic_store(done, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -2227,7 +2294,7 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy)
     return r;
 }
 
-MarchShape choose_march_shape(const RayGeom& rg, int staged_channels)
+MarchShape choose_march_shape(const RayGeom& rg, bool staged_projection)
 {
     MarchShape ms;
     long rays = (long)rg.nu * rg.nv;
@@ -2236,14 +2303,14 @@ MarchShape choose_march_shape(const RayGeom& rg, int staged_channels)
     // through the union of their sample ranges together (measured best on
     // both layouts)
     ms.seg = rays >= 8L * 1024 * 64 ? 1 : (rays >= 4L * 1024 * 64 ? 2 : 4);
-    // Fewer still: eight segments in blocks of eight waves, for one channel.
-    // With under three waves a SIMD a wave's chunks follow each other alone,
-    // so halving their number counts: 256x256x100 onto 128x96 pixels 78 -> 56
-    // us, onto 256x192 57 -> 49 us.  (Images of more channels keep four: a
-    // solve would carry the other grouping of a ray's sum through its line
-    // searches.  It gains 10 % at 128x96 pixels, and 24-byte cells lose 9 % at
-    // 256x192.)
-    if (staged_channels == 1 && rays < 65536) ms.seg = 8;
+    // Fewer still: eight segments in blocks of eight waves, for projections of
+    // one FP32 image.  With under three waves a SIMD a wave's chunks follow
+    // each other alone, so halving their number counts: 256x256x100 onto
+    // 128x96 pixels 78 -> 56 us, onto 256x192 57 -> 49 us.  (Evaluations keep
+    // four: a solve would carry the other grouping of a ray's sum through its
+    // line searches.  Eight gained 10 % at 128x96 pixels, and 24-byte cells
+    // lost 9 % at 256x192.)
+    if (staged_projection && rays < 65536) ms.seg = 8;
     ms.tile_u = 4;
     return ms;
 }
@@ -2479,8 +2546,12 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
     A.y = (const float*)y;
     A.p_out = (float*)p_out;
     A.partials = moments ? partials : nullptr;
-    A.moments = moments;
     int blocks = march_blocks(rg, ms);
+    const bool fused = moments && done && !L.half && ms.seg <= 4 && blocks <= kFusedSumBlocks;
+    A.moments = moments;
+    A.arrived = arrived;
+    A.done = done;
+    A.seq = seq;
     if (L.half && (L.C == 1 || ms.seg > 4)) return hipErrorInvalidValue;
     if (L.half) {
         switch (L.C) {
@@ -2493,7 +2564,8 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
         // every FP32 cell size stages through LDS (8-byte cells too: 11-18 %
         // faster than the gather through the L1 at paper scale, K = 1)
         if (ms.seg > 4 && L.C != 1) return hipErrorInvalidValue;
-#define PCR_ML(...) k_march_lds<__VA_ARGS__><<<blocks, 256, 0, s>>>(A)
+#define PCR_ML(c, kc_) (fused ? k_march_lds<c, kc_, 4, false, true><<<blocks, 256, 0, s>>>(A) \
+                               : k_march_lds<c, kc_><<<blocks, 256, 0, s>>>(A))
         switch (L.C) {
         case 1:
             if (raw)
@@ -2518,7 +2590,7 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
 #undef PCR_ML
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !moments) return e;
+    if (e != hipSuccess || !moments || fused) return e;
     return run_reduce(partials, blocks, n_moments(kc), n_moments(L.C), moments, s, arrived, done, seq);
 }
 
@@ -2707,13 +2779,14 @@ hipError_t launch_absmax_rows(pcr_dtype dt, const void* a, size_t n, int rows, f
 
 hipError_t launch_localize(pcr_dtype storage, const pcr_grid& g, int K, const void* mean,
                            const void* U, const double* w_eff, const double* p_ref, double tol,
-                           int max_iter, double* out, hipStream_t s)
+                           int max_iter, double* out, unsigned long long* done, unsigned long long seq,
+                           hipStream_t s)
 {
     auto w = wvec(w_eff, K);
     PCR_DISPATCH_S(storage, S,
         k_localize<S><<<1, 64, 0, s>>>((const S*)mean, (const S*)U, K, w, vox(g), p_ref[0],
                                        p_ref[1], p_ref[2], g.origin_mm[0], g.origin_mm[1],
-                                       g.origin_mm[2], tol, max_iter, out));
+                                       g.origin_mm[2], tol, max_iter, out, done, seq));
     return hipGetLastError();
 }
 

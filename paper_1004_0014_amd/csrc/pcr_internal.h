@@ -85,9 +85,8 @@ struct MarchShape {
     int seg;             // ray segments (threads) per ray: 1, 2 or 4, or 8 (blocks of
                          // 512 threads; staged march of one channel only)
 };
-// staged_channels: channels per cell of the FP32 march through LDS, 0 for the
-// other marches
-MarchShape choose_march_shape(const RayGeom& rg, int staged_channels);
+// staged_projection: an FP32 projection of one image, without moments
+MarchShape choose_march_shape(const RayGeom& rg, bool staged_projection);
 
 // Moments returned by a ray march over channels (f, h_1..h_K):
 //   0 sum y, 1 sum y^2, 2 sum p, 3 sum y p, 4 sum p^2,
@@ -171,9 +170,11 @@ hipError_t launch_contract(pcr_dtype compute, pcr_dtype storage, pcr_dtype f0_dt
 hipError_t launch_warp_adjoint(pcr_dtype compute, const pcr_grid& g, const void* dvf,
                                const void* gv, void* out, hipStream_t s);
 // Fixed-point localisation; writes out[0..2] = p, out[3] = iterations,
-// out[4] = converged (1) or not (0).
+// out[4] = converged (1) or not (0), then `seq` to *done (system scope: both
+// may point into mapped host memory).
 hipError_t launch_localize(pcr_dtype storage, const pcr_grid& g, int K, const void* mean,
                            const void* U, const double* w_eff, const double* p_ref, double tol,
-                           int max_iter, double* out, hipStream_t s);
+                           int max_iter, double* out, unsigned long long* done, unsigned long long seq,
+                           hipStream_t s);
 
 }  // namespace pcr

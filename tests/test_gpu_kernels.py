@@ -103,3 +103,36 @@ def test_pca_chunks_and_signs(n, J, K, turn):
     assert rel_l2(U.cpu().numpy(), Uo) <= 1e-5
     np.testing.assert_allclose(sing, so, rtol=1e-6)
     np.testing.assert_allclose(wt, wo, rtol=1e-5, atol=1e-5 * np.abs(wo).max())
+
+
+@pytest.mark.parametrize("K", [1, 3, 4, 5, 7])
+def test_final_sums_by_block_count(K):
+    """The final moments by the march's last block (up to 512 blocks of 4 x 16
+    pixels) and by a launch of their own, one after the other in one context:
+    the same sums again on each repeat, and the oracle's within the bounds of
+    FP32 projections (2e-5 for J; 5e-4 for the gradient, whose cells may
+    differ at faces)."""
+    L = _lib()
+    g = S.Grid((24, 20, 16), (3.0, 3.0, 3.0))
+    rng = np.random.default_rng(50 + K)
+    f_t, f = rounded(S.phantom(g, seed=8), torch.float32)
+    zyx = np.indices(g.shape) / 7.0
+    mean_t, mean = rounded(np.stack([2.0 * np.sin(zyx[a] + a) for a in range(3)]), torch.float32)
+    U_t, U = rounded(np.stack([np.stack([np.sin(zyx[(a + k) % 3] * (1 + 0.3 * k) + a) for a in range(3)])
+                               for k in range(K)]), torch.float32)
+    w = rng.uniform(-1.0, 1.0, K)
+    geoms = [S.Geom(math.radians(35.0), nu, nv, 90.0 / nu, 80.0 / nv, 1.5)
+             for nu, nv in ((4, 16), (9, 5), (33, 40), (128, 256), (129, 256))]
+    ctx = L.Context(g, L.DeviceModel(mean_t.to(DEV), U_t.to(DEV)), f_t.to(DEV))
+    x = oracle.warp(g, f, oracle.compose(g, mean, U, 0.3 * w))
+    ys = [torch.tensor(oracle.project(g, G, x), dtype=torch.float32) for G in geoms]
+    first = [ctx.cost_grad(y.to(DEV), G, w, 0.9, 0.01) for y, G in zip(ys, geoms)]
+    for _ in range(3):
+        for y, G, (J, grad) in zip(ys, geoms, first):
+            J2, grad2 = ctx.cost_grad(y.to(DEV), G, w, 0.9, 0.01)
+            assert J2 == J and np.array_equal(grad2, grad), G
+    for y, G, (J, grad) in zip(ys, geoms, first):
+        Jo, go = oracle.cost_grad(g, G, f, mean, U, w, y.double().numpy(), 0.9, 0.01)
+        assert abs(J - Jo) <= 2e-5 * Jo, G
+        assert rel_l2(grad, go) <= 5e-4, G
+    ctx.close()
