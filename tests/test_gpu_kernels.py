@@ -136,3 +136,18 @@ def test_final_sums_by_block_count(K):
         assert abs(J - Jo) <= 2e-5 * Jo, G
         assert rel_l2(grad, go) <= 5e-4, G
     ctx.close()
+
+
+@pytest.mark.parametrize("step", [0.3, 1.99, 2.0, 4.5])
+@pytest.mark.parametrize("ang", [3.0, 95.0, 181.0, 230.0, 275.0])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_backprojection_sample_pairs(step, ang, dtype):
+    """Rays along and against both column axes, with steps below the spacing
+    (two samples a turn, odd counts among them) and from it on (one); the
+    backprojection parity bounds."""
+    L = _lib()
+    g = S.Grid((37, 34, 19), (2.0, 2.0, 2.0))
+    G = S.Geom(math.radians(ang), 37, 29, 3.1, 3.1, step, off_u=0.3, off_v=-0.2)
+    r_t, r = rounded(S.seeded(6, (29, 37)), dtype)
+    bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
+    assert rel_l2(bp, oracle.backproject(g, G, r)) <= (1e-5 if dtype == torch.float32 else 1e-12)
