@@ -309,7 +309,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     y = y_;
     mode = mode_;
     rg = make_ray_geom(*grid, G);
-    ms = choose_march_shape(rg, false);
+    ms = choose_march_shape(rg, compute, false);
     M = G.nu * G.nv;
     blocks = march_blocks(rg, ms);
     const bool yfast = prefer_yfast(G);
@@ -326,7 +326,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     }
     sc->L1 = make_pad(*grid, 1);
     rgc = make_ray_geom(*grid, G, yfast);
-    msc = choose_march_shape(rgc, false);
+    msc = choose_march_shape(rgc, compute, false);
     blocksc = march_blocks(rgc, msc);
     const int dev = sc->device;
     if (mode == PCR_GRAD_FUSED) {
@@ -828,7 +828,7 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     hipStream_t s = (hipStream_t)stream;
     const PadLayout L = make_pad(*grid, 1);
     const RayGeom rg = make_ray_geom(*grid, *geom);
-    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32);
+    const MarchShape ms = choose_march_shape(rg, compute, true);
     if (project_unpadded(compute, rg)) {
         PROF(MARCH, s);
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
@@ -865,7 +865,7 @@ pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geo
                     grid->n[0], grid->n[1], grid->n[2], bytes, (size_t)PCR_NOALLOC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
     const RayGeom rg = make_ray_geom(*grid, *geom);
-    const MarchShape ms = choose_march_shape(rg, compute == PCR_F32);
+    const MarchShape ms = choose_march_shape(rg, compute, true);
     if (project_unpadded(compute, rg)) {
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;

@@ -824,6 +824,11 @@ __global__ void __launch_bounds__(256) k_march(RayGeom g, MarchShape ms, int til
         nsamp = rs.count;
         const long pxy = (long)px * py;
         const Chan<R, C>* base = vol + (1 + px + pxy);   // cell of voxel (0,0,0)
+        // (two samples' loads in flight, for one channel: FP64 256x256x100 onto
+        // 512x384 pixels at 11 / 46 / 86 deg 196 / 234 / 158 -> 174 / 204 / 158
+        // us; four take the registers: 205 / 249 / 188)
+        constexpr int kUnroll = C == 1 ? 2 : 1;
+#pragma unroll kUnroll
         for (int m = 0; m < rs.count; ++m) {
             R fm = (R)m;
             R qx = clampv(fma(fm, rs.dq[0], rs.q0[0]), (R)-1, (R)fnx);
@@ -2322,7 +2327,7 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy)
     return r;
 }
 
-MarchShape choose_march_shape(const RayGeom& rg, bool staged_projection)
+MarchShape choose_march_shape(const RayGeom& rg, pcr_dtype compute, bool projection)
 {
     MarchShape ms;
     long rays = (long)rg.nu * rg.nv;
@@ -2331,14 +2336,18 @@ MarchShape choose_march_shape(const RayGeom& rg, bool staged_projection)
     // through the union of their sample ranges together (measured best on
     // both layouts)
     ms.seg = rays >= 8L * 1024 * 64 ? 1 : (rays >= 4L * 1024 * 64 ? 2 : 4);
-    // Fewer still: eight segments in blocks of eight waves, for projections of
-    // one FP32 image.  With under three waves a SIMD a wave's chunks follow
-    // each other alone, so halving their number counts: 256x256x100 onto
-    // 128x96 pixels 78 -> 56 us, onto 256x192 57 -> 49 us.  (Evaluations keep
-    // four: a solve would carry the other grouping of a ray's sum through its
-    // line searches.  Eight gained 10 % at 128x96 pixels, and 24-byte cells
-    // lost 9 % at 256x192.)
-    if (staged_projection && rays < 65536) ms.seg = 8;
+    // Fewer still, for plain projections: eight segments in blocks of eight
+    // waves where an FP32 image is staged.  With under three waves a SIMD a
+    // wave's chunks follow each other alone, so halving their number counts:
+    // 256x256x100 onto 128x96 pixels 78 -> 56 us, onto 256x192 57 -> 49 us.
+    // In FP64 a wave's samples wait for their loads one pair after the other,
+    // and sixteen segments pay below 16384 rays: 40^3 onto 64x48 pixels 25 ->
+    // 15 us (at 203x151, 0-10 % either way by angle).  (Evaluations keep four:
+    // a solve would carry the other grouping of a ray's sum through its line
+    // searches.  Eight gained 10 % at 128x96 pixels, and 24-byte cells lost
+    // 9 % at 256x192.)
+    if (projection && compute == PCR_F32 && rays < 65536) ms.seg = 8;
+    if (projection && compute == PCR_F64 && rays < 16384) ms.seg = 16;
     ms.tile_u = 4;
     return ms;
 }

@@ -82,11 +82,11 @@ RayGeom make_ray_geom(const pcr_grid& g, const pcr_geom& G, bool swap_xy = false
 // Launch shape of the ray-march kernels.
 struct MarchShape {
     int tile_u;          // pixels along u covered by one wave (64 / tile_u rows)
-    int seg;             // ray segments (threads) per ray: 1, 2 or 4, or 8 (blocks of
-                         // 512 threads; staged march of one channel only)
+    int seg;             // ray segments (threads) per ray: 1, 2, 4 or 16, or 8 (blocks
+                         // of 512 threads; staged march of one channel only)
 };
-// staged_projection: an FP32 projection of one image, without moments
-MarchShape choose_march_shape(const RayGeom& rg, bool staged_projection);
+// projection: of one image, without moments
+MarchShape choose_march_shape(const RayGeom& rg, pcr_dtype compute, bool projection);
 
 // Moments returned by a ray march over channels (f, h_1..h_K):
 //   0 sum y, 1 sum y^2, 2 sum p, 3 sum y p, 4 sum p^2,

@@ -151,3 +151,16 @@ def test_backprojection_sample_pairs(step, ang, dtype):
     r_t, r = rounded(S.seeded(6, (29, 37)), dtype)
     bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
     assert rel_l2(bp, oracle.backproject(g, G, r)) <= (1e-5 if dtype == torch.float32 else 1e-12)
+
+
+@pytest.mark.parametrize("nu,nv,step", [(1, 1, 0.1), (5, 3, 1.0), (67, 50, 0.7), (128, 128, 2.5), (129, 128, 2.5)])
+def test_f64_projection_segments(nu, nv, step):
+    """FP64 projections in sixteen segments (below 128 x 128 rays) and four,
+    with ragged tiles and counts of samples that leave empty segments; the FP64
+    parity bound of 1e-12."""
+    L = _lib()
+    g = S.Grid((23, 21, 17), (2.0, 2.0, 2.0))
+    G = S.Geom(math.radians(33.0), nu, nv, 70.0 / nu, 60.0 / nv, step, off_u=0.4)
+    x = S.seeded(8, g.shape, "uniform")
+    p = L.forward_project(g, G, torch.tensor(x, dtype=torch.float64, device=DEV)).cpu().numpy()
+    assert rel_l2(p, oracle.project(g, G, x)) <= 1e-12
