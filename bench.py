@@ -303,9 +303,11 @@ def roofline(W, prof, samples_per_launch, channels, cell_bytes, traffic_profile=
         achieved = flops / avg_s / 1e12
         traffic = profiled_traffic(traffic_profile) if traffic_profile else None
         # what binds it, from the counter profile of the same kernel: VALU
-        # issue (wave-instructions per CU and clock, at most one), with the
-        # vector L1's tag lookups beside it
+        # issue (wave-instructions per CU and clock, against the rate that
+        # independent FMAs reach), with the vector L1's tag lookups beside it
         cprof = "march_counters_256x256x100_f32"
+        issue = profiled_value(cprof, "valu_issue_fraction")
+        issue_peak = profiled_value(cprof, "valu_issue_peak")
         tags = profiled_value(cprof, "l1_tag_lookups_per_cu_clock")
         taps_gbs = samples_per_launch * 8 * cell_bytes / avg_s / 1e9
         return {"kernel": dom, "bound": "alu", "achieved": achieved, "peak": FP32_VECTOR_PEAK_TFLOPS,
@@ -315,8 +317,8 @@ def roofline(W, prof, samples_per_launch, channels, cell_bytes, traffic_profile=
                 "algorithmic_flops_per_launch": flops,
                 "binding_resource": {
                     "name": "VALU issue (SQ_ACTIVE_INST_VALU per CU and clock)",
-                    "achieved_per_cu_clock": profiled_value(cprof, "valu_issue_fraction"),
-                    "peak_per_cu_clock": 1.0, "frac": profiled_value(cprof, "valu_issue_fraction"),
+                    "achieved_per_cu_clock": issue, "peak_per_cu_clock": issue_peak,
+                    "frac": issue / issue_peak if issue and issue_peak else None,
                     "l1_tag_lookups_per_cu_clock": tags,
                     "source": "profiles/%s.md" % cprof},
                 "hbm": {"dram_bytes_per_launch": traffic,

@@ -1178,9 +1178,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
 // box cost six reductions a chunk and the copy 19 instructions per 64 cells),
 // no clamps where the box lies inside the image, and no registers or waits in
 // the copy.  Measured (march alone, before -> now): K = 3 at 256x256x100,
-// 512x384 pixels, 57 deg: 160.5 -> 144 us; one channel there: 163 -> 140 us;
-// K = 4 at 256x256x128: 205 -> 172 us; K = 5 at 512x512x160, 1024x768 pixels:
-// 1531 -> 1227 us.  Most of the gain at K = 4 and 5 is the staging of 24-byte
+// 512x384 pixels, 57 deg: 160.5 -> 144 us (136 with the ray set-up and the
+// moments of today); one channel there: 163 -> 140 us (126 from the unpadded
+// volume); K = 4 at 256x256x128: 205 -> 172 us (168); K = 5 at 512x512x160,
+// 1024x768 pixels: 1531 -> 1227 us.  Most of the gain at K = 4 and 5 is the staging of 24-byte
 // cells as planes of 16 and 4 bytes: three 8-byte reads a cell pair kept the
 // LDS busy 0.77 of the clocks, 16 + 4 byte reads 0.55.
 // LDS per wave: six 256-thread blocks per CU at C <= 4 (72 VGPRs), five at
