@@ -1785,6 +1785,9 @@ template <> __device__ __forceinline__ double fract_of<double>(double x) { retur
 // x clamped to [0, 1] (x <= 1 where it is used)
 __device__ __forceinline__ float saturate(float x) { return __builtin_amdgcn_fmed3f(x, 0.f, 1.f); }
 __device__ __forceinline__ double saturate(double x) { return fmax(x, 0.0); }
+// the whole voxel of a position along a column, kept inside the run of slots
+__device__ __forceinline__ float run_voxel(float x, float hi) { return __builtin_amdgcn_fmed3f(floorf(x), -10.f, hi); }
+__device__ __forceinline__ double run_voxel(double x, double hi) { return fmin(fmax(floor(x), -10.0), hi); }
 
 // What bounds the column gather is the latency of a sample's round trip to
 // its LDS run (position, read, add, write: the next sample may touch the same
@@ -1796,9 +1799,11 @@ __device__ __forceinline__ double saturate(double x) { return fmax(x, 0.0); }
 // rays (six blocks) 752 / 630 / 710 us; 8 x 4 or 4 x 8 columns with 8 lanes
 // each 750-1570 us; LDS float atomics instead of the round trip 5000-5900 us
 // (they take the lanes one by one).  Two samples a turn (PAIR) halve the round
-// trips for 35 VALU instructions a turn: 722 / 569 / 662 us; with the ray's
-// weight applied in the last additions and whole sample bounds as floats
-// 701 / 547 / 644 us.  (Loading the next ray's record ahead: 3-4 % slower.)
+// trips: 722 / 569 / 662 us; with the ray's weight applied in the last
+// additions, whole sample bounds as floats and positions from the column's
+// middle (error against FP64 7.4e-8 - 1.1e-7 relative, 7.9e-8 - 1.5e-7 from
+// the brick's corner) 718 / 552 / 653 us, 33 VALU instructions a turn.
+// (Loading the next ray's record ahead: 3-4 % slower.)
 constexpr int kBpTileU = 8, kBpTileV = 32;   // staged rays: one per thread
 // CB x CB columns a brick (along the other in-plane axis and z), the block's
 // 256 threads split evenly over them.  PAIR: no ray moves more than a voxel a
@@ -1812,7 +1817,9 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     // One staged ray in records of consecutive rays, so the lanes of a
     // column, which take consecutive rays, read without bank conflicts.  Axes
     // in column order (A, B, z):
-    //   s_r0: the sample nearest the brick centre minus the brick origin, r dt
+    //   s_r0: the sample nearest the brick centre minus the brick origin (along
+    //   A minus the column's middle, so that positions along it round finest),
+    //   r dt
     //   s_r1: the index-space step per sample, slab lower bound along A
     //   s_r2: 1/step in B and z; s_r3: slab upper bound along A
     // Slab bounds are in samples: |q_a + m d_a - l| < 1 for m within |1/d_a|
@@ -1842,7 +1849,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     const int col = t / LPC, lane = t % LPC;        // column (lb, lz) and ray lane
     const int lb = col % CB, lz = col / CB;
     for (int e = t; e < 256 * 20; e += 256) s_acc[e] = (R)0;
-    R* acc = s_acc + t;
+    R* acc = s_acc + 10 * 256 + t;   // the slot of the voxel at the column's middle
     if (t == 0) {
         const float lo[3] = {(float)(b0[0] - 1), (float)(b0[1] - 1), (float)(b0[2] - 1)};
         const float hi[3] = {(float)(b0[0] + A.bx), (float)(b0[1] + A.by), (float)(b0[2] + A.bz)};
@@ -1940,7 +1947,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 // whole numbers)
                 const float la = __builtin_amdgcn_fmed3f(fmaxf(lo[AX], (float)m0 - 0.5f), -1.0e6f, 1.0e6f);
                 const float ha = __builtin_amdgcn_fmed3f(fminf(hi[AX], (float)m1 + 0.5f), -1.0e6f, 1.0e6f);
-                s_r0[t] = {(R)qr[AX], (R)qr[BX], (R)qr[2], rw};
+                s_r0[t] = {(R)(qr[AX] - 8.0), (R)qr[BX], (R)qr[2], rw};
                 s_r1[t] = {(R)dq[AX], (R)dq[BX], (R)dq[2], (R)la};
                 s_r2[t] = make_float2(inv[BX], inv[2]);
                 s_r3[t] = ha;
@@ -1976,7 +1983,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 const float2 r2 = s_r2[k];
                 const float ha = s_r3[k];
                 // |q + m d - l| < 1 for m within |1/d| of (l - q) / d
-                const R qa = r0.x + (R)2, qb = r0.y - rlb, qz = r0.z - rlz;
+                const R qa = r0.x, qb = r0.y - rlb, qz = r0.z - rlz;
                 const float cb_ = -(float)qb * r2.x, cz_ = -(float)qz * r2.y;
                 float lo = fmaxf(fmaxf((float)r1.w, cb_ - fabsf(r2.x)), cz_ - fabsf(r2.y));
                 float hi = fminf(fminf(ha, cb_ + fabsf(r2.x)), cz_ + fabsf(r2.y));
@@ -1996,14 +2003,16 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                     // two samples a turn, less than a voxel apart along A:
                     // they touch three voxels of the run
                     for (R fm = (R)lo; fm <= fm1; fm += (R)2) {
-                        const R pb = fma(fm, db, qb), pz = fma(fm, dz, qz), xa = fma(fm, da, qa);
+                        const R xa = fma(fm, da, qa), fl = run_voxel(xa, (R)7);
+                        R* a3 = acc + (int)fl * 256;
+                        const R s0 = a3[0], s1 = a3[256], s2 = a3[512];
+                        // (the reads go out before the weights are formed)
+                        __builtin_amdgcn_sched_barrier(0);
+                        const R x1 = xa - fl, x2 = x1 + da;
+                        const R pb = fma(fm, db, qb), pz = fma(fm, dz, qz);
                         const R w1 = saturate((R)1 - fabs(pb)) * saturate((R)1 - fabs(pz));
                         R w2 = saturate((R)1 - fabs(pb + db)) * saturate((R)1 - fabs(pz + dz));
                         w2 = fm < fm1 ? w2 : (R)0;
-                        const int j = min(max((int)xa, 0), 17);
-                        const R x1 = xa - (R)j, x2 = x1 + da;
-                        R* a3 = acc + j * 256;
-                        const R s0 = a3[0], s1 = a3[256], s2 = a3[512];
                         const R u0 = w1 * saturate((R)1 - x1), v0 = w2 * saturate((R)1 - x2), v2 = w2 * saturate(x2 - (R)1);
                         a3[0] = fma(rw, u0 + v0, s0);
                         a3[256] = fma(rw, (w1 - u0) + (w2 - v0 - v2), s1);
@@ -2014,11 +2023,10 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                     // (saturated differences: one instruction each in FP32)
                     const R wbz = saturate((R)1 - fabs(fma(fm, db, qb))) *
                                   (saturate((R)1 - fabs(fma(fm, dz, qz))) * rw);
-                    // two voxels into the run, so that truncation is the floor;
-                    // the slab range keeps xa within (0.99, 18.01): the clamp
+                    // the slab range keeps xa within (-9.01, 8.01): the clamp
                     // only guards the LDS run
                     const R xa = fma(fm, da, qa);
-                    const int j = min(max((int)xa, 0), 18);
+                    const int j = (int)run_voxel(xa, (R)8);
                     const R t1 = fract_of(xa) * wbz, t0 = wbz - t1;
                     // the thread's own LDS run: a plain read-modify-write
                     acc[j * 256] += t0;
