@@ -207,9 +207,9 @@ pcr_status pcr_warp_contract(const pcr_grid* grid, const pcr_model* model, pcr_d
 
 /* Forward projection P vol (eq. (2)'s projection matrix, discretised as in
  * the conventions above).  vol_dev [N] and proj_dev [nv][nu] of dtype
- * `compute` (F32 or F64); proj_dev is overwritten.  FP64 and coarse
- * detectors march a zero-padded device copy of the volume (library-owned
- * scratch, reused). */
+ * `compute` (F32 or F64); proj_dev is overwritten, and may share memory with
+ * vol_dev.  FP64, coarse detectors and shared memory march a zero-padded
+ * device copy of the volume (library-owned scratch, reused). */
 pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom,
                                pcr_dtype compute, const void* vol_dev, void* proj_dev,
                                void* stream);

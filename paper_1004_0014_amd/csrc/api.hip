@@ -697,6 +697,16 @@ pcr_status scratch_on_device(int dev, void** out)
     return PCR_OK;
 }
 
+// Whether a projection may read the volume itself (see project_unpadded).
+// One written over its own volume marches a copy, made before the first
+// pixel is stored.
+bool reads_volume(pcr_dtype compute, const RayGeom& rg, const PadLayout& L, const void* vol, const void* proj)
+{
+    const uintptr_t v = (uintptr_t)vol, p = (uintptr_t)proj;
+    const size_t es = dtype_size(compute), nv = (size_t)L.nx * L.ny * L.nz * es, np = (size_t)rg.nu * rg.nv * es;
+    return project_unpadded(compute, rg) && (v + nv <= p || p + np <= v);
+}
+
 struct DeviceGuard {
     int prev = -1;
     bool ok = false;
@@ -829,7 +839,7 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     const PadLayout L = make_pad(*grid, 1);
     const RayGeom rg = make_ray_geom(*grid, *geom);
     const MarchShape ms = choose_march_shape(rg, compute, true);
-    if (project_unpadded(compute, rg)) {
+    if (reads_volume(compute, rg, L, vol_dev, proj_dev)) {
         PROF(MARCH, s);
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;
@@ -866,7 +876,7 @@ pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geo
     hipStream_t s = (hipStream_t)stream;
     const RayGeom rg = make_ray_geom(*grid, *geom);
     const MarchShape ms = choose_march_shape(rg, compute, true);
-    if (project_unpadded(compute, rg)) {
+    if (reads_volume(compute, rg, L, vol_dev, proj_dev)) {
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;
     }
