@@ -326,12 +326,13 @@ __global__ void __launch_bounds__(256) k_compose(const S* __restrict__ mean, con
 // --------------------------------------------------------------- warp ----
 // x / s for a grid constant s, given rs = RN(1 / s): a product and one
 // correction step (Markstein), the correctly rounded quotient of a normal
-// result at a third of the instructions of a division.
+// result at a third of the instructions of a division.  Of an infinity (or
+// of a product that overflows) the correction is NaN and the product stands.
 template <typename R>
 __device__ __forceinline__ R div_by(R x, R s, R rs)
 {
-    const R q = x * rs;
-    return fma(fma(-q, s, x), rs, q);
+    const R q = x * rs, c = fma(fma(-q, s, x), rs, q);
+    return c == c ? c : q;
 }
 
 // Trilinear sample of an unpadded image at index-space point q, zero outside;

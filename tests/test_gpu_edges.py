@@ -64,3 +64,23 @@ def test_backprojection_of_a_pixel_that_is_not_finite(value, step, n, du, dtype)
         assert np.isnan(reached).all() if math.isnan(value) else (reached == value).all()
         assert rel_l2(got[weight == 0], rest[weight == 0]) <= (1e-5 if dtype == torch.float32 else 1e-12)
         r[iv, iu] = 0.0
+
+
+@pytest.mark.parametrize("compute", [torch.float32, torch.float64])
+def test_infinite_gradient_of_an_infinite_voxel(compute):
+    """A reference image of -inf at its last corner, moved by less than a voxel
+    against every axis: the derivatives there are -inf, so with rising fields,
+    a bright measurement and a, b > 0 every term of J and of its gradient is
+    +inf, and none is NaN."""
+    L = _lib()
+    g = S.Grid((12, 10, 8), (2.0, 2.5, 3.0))
+    f = torch.zeros(g.shape, dtype=compute)
+    f[-1, -1, -1] = -math.inf
+    mean = torch.full((3,) + g.shape, -0.7, dtype=compute)
+    U = torch.full((1, 3) + g.shape, 0.1, dtype=compute)
+    G = S.Geom(0.3, 40, 33, 1.7, 1.7, 0.9, off_u=0.21, off_v=0.13)
+    ctx = L.Context(g, L.DeviceModel(mean.to(DEV), U.to(DEV)), f.to(DEV), compute=compute)
+    y = torch.ones((33, 40), dtype=compute, device=DEV)
+    J, grad = ctx.cost_grad(y, G, [0.5], 0.9, 0.1)
+    ctx.close()
+    assert J == math.inf and grad[0] == math.inf
