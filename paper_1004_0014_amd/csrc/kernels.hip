@@ -1807,9 +1807,17 @@ __device__ __forceinline__ double run_voxel(double x, double hi) { return fmin(f
 // (Loading the next ray's record ahead: 3-4 % slower.)
 constexpr int kBpTileU = 8, kBpTileV = 32;   // staged rays: one per thread
 // CB x CB columns a brick (along the other in-plane axis and z), the block's
-// 256 threads split evenly over them.  PAIR: no ray moves more than a voxel a
-// sample along A, so two neighbouring samples touch three voxels of the run.
-template <typename R, int CB, bool PAIR>
+// 256 threads split evenly over them.  MODE: how a lane goes through a ray's
+// samples.
+//   kPairs: no ray moves more than a voxel a sample along A, so two
+//   neighbouring samples touch three voxels of the run
+//   kSingles: one sample a turn
+//   kMany: one sample a turn with an integer index, where a brick may hold
+//   samples further than kBpReach from the one nearest its centre, the end of
+//   the other modes' bounds
+enum { kPairs, kSingles, kMany };
+constexpr float kBpReach = 1.0e6f;
+template <typename R, int CB, int MODE>
 __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* __restrict__ resid,
                                                              const R* __restrict__ p,
                                                              const R* __restrict__ y,
@@ -1840,6 +1848,8 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     __shared__ R s_acc[20 * 256];
     __shared__ int s_box[4];
     __shared__ int s_odd;   // whether a ray staged so far is infinite or NaN
+    // kMany: the rays' valid samples
+    __shared__ int2 s_valid[MODE == kMany ? NR : 1];
     const RayGeom& g = A.g;
     const int t = threadIdx.x;
     const int bid = blockIdx.x;
@@ -1922,7 +1932,7 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                         m0 = -(int)nc;
                         m1 = (int)(nlast - nc);
                         rw = (R)(r * g.dt);
-                        if (PAIR && dq[AX] < 0.0) {   // samples in rising order along A
+                        if (MODE == kPairs && dq[AX] < 0.0) {   // samples in rising order along A
                             const int n0 = m0;
                             m0 = -m1;
                             m1 = -n0;
@@ -1947,13 +1957,21 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                     lo[ax] = fminf(e1, e2);
                     hi[ax] = fmaxf(e1, e2);
                 }
-                // the valid samples [m0, m1] narrow the bounds along A: with
-                // the half-sample margin the rounding below yields exactly
-                // max(m0, .) and min(m1, .) (|m| < 2^22 where they bind)
-                // (clamped, so that a sample index stays far inside a float's
-                // whole numbers)
-                const float la = __builtin_amdgcn_fmed3f(fmaxf(lo[AX], (float)m0 - 0.5f), -1.0e6f, 1.0e6f);
-                const float ha = __builtin_amdgcn_fmed3f(fminf(hi[AX], (float)m1 + 0.5f), -1.0e6f, 1.0e6f);
+                float la, ha;
+                if constexpr (MODE == kMany) {
+                    // (widened by the rounding of a position in the column)
+                    la = lo[AX] - fabsf(1.0e-5f * inv[AX]);
+                    ha = hi[AX] + fabsf(1.0e-5f * inv[AX]);
+                    s_valid[t] = make_int2(m0, m1);
+                } else {
+                    // the valid samples [m0, m1] narrow the bounds along A:
+                    // with the half-sample margin the rounding below yields
+                    // exactly max(m0, .) and min(m1, .); no sample of the brick
+                    // is beyond kBpReach, where both are whole numbers and
+                    // halves of a float's
+                    la = __builtin_amdgcn_fmed3f(fmaxf(lo[AX], (float)m0 - 0.5f), -kBpReach, kBpReach);
+                    ha = __builtin_amdgcn_fmed3f(fminf(hi[AX], (float)m1 + 0.5f), -kBpReach, kBpReach);
+                }
                 s_r0[t] = {(R)(qr[AX] - 8.0), (R)qr[BX], (R)qr[2], rw};
                 s_r1[t] = {(R)dq[AX], (R)dq[BX], (R)dq[2], (R)la};
                 s_r2[t] = make_float2(inv[BX], inv[2]);
@@ -1996,34 +2014,47 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                 const float cb_ = -(float)qb * r2.x, cz_ = -(float)qz * r2.y;
                 float lo = fmaxf(fmaxf((float)r1.w, cb_ - fabsf(r2.x)), cz_ - fabsf(r2.y));
                 float hi = fminf(fminf(ha, cb_ + fabsf(r2.x)), cz_ + fabsf(r2.y));
-                // whole samples, as floats (exact: |m| <= 1e6 between the
-                // clamped bounds along A)
+                const R da = r1.x, db = r1.y, dz = r1.z;
+                const R rw = r0.w;
+                // one sample, to the voxels of nonzero weight alone
+                auto single = [&](R fm) {
+                    const R xa = fma(fm, da, qa), fl = run_voxel(xa, (R)8);
+                    R* a2 = acc + (int)fl * 256;
+                    const R w = saturate((R)1 - fabs(fma(fm, db, qb))) * saturate((R)1 - fabs(fma(fm, dz, qz)));
+                    const R w1 = w * (xa - fl), w0 = w - w1;
+                    if (w0 > (R)0) a2[0] = fma(rw, w0, a2[0]);
+                    if (w1 > (R)0) a2[256] = fma(rw, w1, a2[256]);
+                };
+                if constexpr (MODE == kMany) {
+                    // (widened by the rounding of the bounds: the weights
+                    // clip any sample admitted)
+                    const float eb = 1.0e-5f * (fabsf(cb_) + fabsf(r2.x)), ez = 1.0e-5f * (fabsf(cz_) + fabsf(r2.y));
+                    lo = fmaxf(fmaxf((float)r1.w, cb_ - fabsf(r2.x) - eb), cz_ - fabsf(r2.y) - ez) - 1.0f;
+                    hi = fminf(fminf(ha, cb_ + fabsf(r2.x) + eb), cz_ + fabsf(r2.y) + ez) + 1.0f;
+                    const int2 valid = s_valid[k];
+                    const int m0 = max(valid.x, (int)__builtin_amdgcn_fmed3f(lo, -2.1e9f, 2.1e9f));
+                    const int m1 = min(valid.y, (int)__builtin_amdgcn_fmed3f(hi, -2.1e9f, 2.1e9f));
+                    for (int m = m0; m <= m1; ++m) single((R)m);
+                    continue;
+                }
+                // whole samples, as floats (exact: |m| <= kBpReach between the
+                // bounds along A)
                 lo = ceilf(lo - 1.0e-3f);
                 hi = floorf(hi + 1.0e-3f);
                 if (!(lo <= hi)) continue;
-                const R da = r1.x, db = r1.y, dz = r1.z;
-                const R rw = r0.w;
                 const R fm1 = (R)hi;
                 // From the first tile with an infinite or NaN ray on, a brick's
-                // rays go sample by sample to the voxels of nonzero weight
-                // alone (below, 0 x inf would reach the others of the run and
-                // inf - inf stand for a weight).
+                // rays go sample by sample (below, 0 x inf would reach the
+                // run's other voxels and inf - inf stand for a weight).
                 if (odd) {
-                    for (R fm = (R)lo; fm <= fm1; fm += (R)1) {
-                        const R xa = fma(fm, da, qa), fl = run_voxel(xa, (R)8);
-                        R* a2 = acc + (int)fl * 256;
-                        const R w = saturate((R)1 - fabs(fma(fm, db, qb))) * saturate((R)1 - fabs(fma(fm, dz, qz)));
-                        const R w1 = w * (xa - fl), w0 = w - w1;
-                        if (w0 > (R)0) a2[0] = fma(rw, w0, a2[0]);
-                        if (w1 > (R)0) a2[256] = fma(rw, w1, a2[256]);
-                    }
+                    for (R fm = (R)lo; fm <= fm1; fm += (R)1) single(fm);
                     continue;
                 }
                 // the ray's values are in registers before the loop starts,
                 // so no wait inside it holds back for the previous sample's
                 // LDS write
                 __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-                if constexpr (PAIR) {
+                if constexpr (MODE == kPairs) {
                     // two samples a turn, less than a voxel apart along A:
                     // they touch three voxels of the run
                     for (R fm = (R)lo; fm <= fm1; fm += (R)2) {
@@ -2789,8 +2820,20 @@ hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeo
     // two samples a turn where no ray moves a voxel or more a sample along A
     // (3-9 % faster at every angle); from there on they touch four voxels or
     // more, one sample's two at a time
-    const bool pair = rg.dt * 1.001 <= rg.sp[A.ax];
-    if (blocks < 1024) {
+    const int mode = rg.dt * 1.001 <= rg.sp[A.ax] ? kPairs : kSingles;
+    // steps so small that the half diagonal of a brick and its margin of a
+    // voxel holds more samples than the bounds of these modes count
+    double diag = 0.0;
+    for (int ax = 0; ax < 3; ++ax) {
+        const double e = 0.5 * ((ax == A.ax ? 16 : 4) + 1) * rg.sp[ax];
+        diag += e * e;
+    }
+    const bool many = std::sqrt(diag) * rg.inv_dt + 2.0 > (double)kBpReach;
+#define PCR_BP(CB, MODE) \
+    k_backproject_columns<R, CB, MODE><<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p, (const R*)y, (R*)out)
+    if (many) {
+        PCR_DISPATCH_R(compute, R, PCR_BP(4, kMany));
+    } else if (blocks < 1024) {
         // fewer than the chip holds at once (five per CU): 2 x 2 columns make
         // four times the blocks, each column with 64 lanes for its rays
         // (51x57x41 voxels, 623x462 pixels: 4.4 -> 0.54 ms; 48x48x32, 128x96:
@@ -2798,14 +2841,11 @@ hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeo
         // the two are equal; beyond, the rays staged once per brick count: 4096
         // blocks 99 against 165 us.
         blocks = bricks(2);
-        PCR_DISPATCH_R(compute, R,
-            auto kern = pair ? k_backproject_columns<R, 2, true> : k_backproject_columns<R, 2, false>;
-            kern<<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p, (const R*)y, (R*)out));
+        PCR_DISPATCH_R(compute, R, if (mode == kPairs) PCR_BP(2, kPairs); else PCR_BP(2, kSingles));
     } else {
-        PCR_DISPATCH_R(compute, R,
-            auto kern = pair ? k_backproject_columns<R, 4, true> : k_backproject_columns<R, 4, false>;
-            kern<<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p, (const R*)y, (R*)out));
+        PCR_DISPATCH_R(compute, R, if (mode == kPairs) PCR_BP(4, kPairs); else PCR_BP(4, kSingles));
     }
+#undef PCR_BP
     return hipGetLastError();
 }
 

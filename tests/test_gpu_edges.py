@@ -84,3 +84,19 @@ def test_infinite_gradient_of_an_infinite_voxel(compute):
     J, grad = ctx.cost_grad(y, G, [0.5], 0.9, 0.1)
     ctx.close()
     assert J == math.inf and grad[0] == math.inf
+
+
+@pytest.mark.parametrize("ang", [20.0, 110.0, 200.0])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_backprojection_of_millions_of_samples(ang, dtype):
+    """A step so small that a ray takes over a million samples on either side
+    of a brick's middle.  A voxel sums up to 400 000 of them in a chain, each
+    addition within half an ulp of the sum: 400 000 x 2^-24 or 2^-53, and 1e-11
+    for the positions (1e-16 x 1e6 samples x 0.1) in FP64."""
+    L = _lib()
+    g = S.Grid((5, 4, 3), (2.0, 2.0, 2.0))
+    G = S.Geom(math.radians(ang), 3, 2, 4.0, 4.0, 1.2e-5, sad=100.0, sdd=150.0, off_u=0.3)
+    r_t, r = rounded(S.seeded(9, (2, 3)), dtype)
+    bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
+    bound = 4e5 * 2.0 ** -24 if dtype == torch.float32 else 4e5 * 2.0 ** -53 + 1e-11
+    assert rel_l2(bp, oracle.backproject(g, G, r)) <= bound
