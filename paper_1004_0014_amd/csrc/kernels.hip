@@ -601,16 +601,20 @@ __global__ void __launch_bounds__(256) k_warp_fused_yf(const F* __restrict__ f0,
     }
 }
 
-// The padded copy of a volume, zero borders included.
+// The padded copy of a volume, zero borders included.  (A block takes more
+// than one slice only of the longest grids, whose padded slices are more than
+// a launch's blocks along z.)
 template <typename R>
 __global__ void __launch_bounds__(256) k_pad(const R* __restrict__ vol, VoxGrid g, R* __restrict__ pad)
 {
-    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y, k = blockIdx.z;
+    const int i = blockIdx.x * 64 + threadIdx.x, j = blockIdx.y * 4 + threadIdx.y;
     if (i >= g.nx + 3 || j >= g.ny + 3) return;
-    const bool in = (unsigned)(i - 1) < (unsigned)g.nx && (unsigned)(j - 1) < (unsigned)g.ny &&
-                    (unsigned)(k - 1) < (unsigned)g.nz;
-    pad[(size_t)i + (size_t)(g.nx + 3) * ((size_t)j + (size_t)(g.ny + 3) * k)] =
-        in ? vol[(size_t)(i - 1) + (size_t)g.nx * ((size_t)(j - 1) + (size_t)g.ny * (k - 1))] : (R)0;
+    for (int k = blockIdx.z; k < g.nz + 3; k += gridDim.z) {
+        const bool in = (unsigned)(i - 1) < (unsigned)g.nx && (unsigned)(j - 1) < (unsigned)g.ny &&
+                        (unsigned)(k - 1) < (unsigned)g.nz;
+        pad[(size_t)i + (size_t)(g.nx + 3) * ((size_t)j + (size_t)(g.ny + 3) * k)] =
+            in ? vol[(size_t)(i - 1) + (size_t)g.nx * ((size_t)(j - 1) + (size_t)g.ny * (k - 1))] : (R)0;
+    }
 }
 
 __global__ void __launch_bounds__(256) k_zero16(uint4* __restrict__ p, size_t n16)
@@ -2566,7 +2570,7 @@ hipError_t launch_pad(pcr_dtype compute, const PadLayout& L, const void* vol, vo
     pcr_grid g{};
     g.n[0] = L.nx; g.n[1] = L.ny; g.n[2] = L.nz;
     g.spacing_mm[0] = g.spacing_mm[1] = g.spacing_mm[2] = 1.0;
-    const dim3 grid((L.px + 63) / 64, (L.py + 3) / 4, L.pz);
+    const dim3 grid((L.px + 63) / 64, (L.py + 3) / 4, std::min(L.pz, 65535));
     PCR_DISPATCH_R(compute, R,
         k_pad<R><<<grid, dim3(64, 4), 0, s>>>((const R*)vol, vox(g), (R*)padded));
     return hipGetLastError();

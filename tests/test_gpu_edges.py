@@ -100,3 +100,18 @@ def test_backprojection_of_millions_of_samples(ang, dtype):
     bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
     bound = 4e5 * 2.0 ** -24 if dtype == torch.float32 else 4e5 * 2.0 ** -53 + 1e-11
     assert rel_l2(bp, oracle.backproject(g, G, r)) <= bound
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("nz", [65533, 65535])
+def test_projection_of_the_longest_grid(nz, noalloc):
+    """As many slices as a grid may have, in FP64, which marches a padded copy:
+    the projection parity bound."""
+    L = _lib()
+    g = S.Grid((3, 2, nz), (2.0, 2.0, 0.01))
+    G = S.Geom(0.5, 24, 30, 0.4, 25.0, 0.7)
+    x = S.seeded(5, g.shape, "uniform")
+    out = torch.empty((30, 24), dtype=torch.float64, device=DEV)
+    vol = torch.tensor(x, dtype=torch.float64, device=DEV)
+    (L.forward_project_noalloc if noalloc else L.forward_project)(g, G, vol, out)
+    assert rel_l2(out.cpu().numpy(), oracle.project(g, G, x)) <= 1e-12
