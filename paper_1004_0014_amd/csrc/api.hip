@@ -223,7 +223,7 @@ void Scratch::release()
     acc1.release();
     p.release();
     partials.release();
-    moments.release();
+    arrived.release();
     host.release();
 }
 
@@ -329,6 +329,8 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     msc = choose_march_shape(rgc, compute, false);
     blocksc = march_blocks(rgc, msc);
     const int dev = sc->device;
+    if (!sc->settled) sc->volc_zeroed = sc->vol1_zeroed = sc->arrived_zeroed = false;
+    sc->settled = false;
     if (mode == PCR_GRAD_FUSED) {
         const size_t need = sc->Lc.cells() * sc->Lc.cell_bytes(esz);
         bool fresh = sc->volc.p == nullptr || sc->volc.bytes < need;
@@ -339,6 +341,7 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
             // layout's cells are read (a serving slot's buffer is sized for
             // its largest stream)
             PROF(ZERO, s);
+            sc->volc_zeroed = false;
             HIP_TRY(launch_zero(sc->volc.p, need, s));
             sc->volc_layout = sc->Lc;
             sc->volc_zeroed = true;
@@ -347,9 +350,11 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
         size_t b1 = sc->L1.cells() * esz;
         bool fresh = sc->vol1.p == nullptr || sc->vol1.bytes < b1;
         PCR_TRY(sc->vol1.ensure(b1, dev, s));
-        if (fresh) {
+        if (fresh || !sc->vol1_zeroed) {
             PROF(ZERO, s);
+            sc->vol1_zeroed = false;
             HIP_TRY(launch_zero(sc->vol1.p, sc->vol1.bytes, s));
+            sc->vol1_zeroed = true;
         }
         PCR_TRY(sc->acc1.ensure((size_t)grid->n[0] * grid->n[1] * grid->n[2] * esz, dev, s));
         PCR_TRY(sc->p.ensure((size_t)M * esz, dev, s));
@@ -358,11 +363,10 @@ pcr_status Evaluator::prepare(const void* y_, const pcr_geom& G, int mode_)
     PCR_TRY(sc->partials.ensure((size_t)std::max(std::max(blocks, blocksc), cblocks) * kMaxMoments *
                                     sizeof(double),
                                 dev, s));
-    // the moments, then the word in which the final sum's workgroups count
-    // themselves (zero between launches)
-    if (!sc->moments.p) {
-        PCR_TRY(sc->moments.ensure((kMaxMoments + 1) * sizeof(double), dev, s));
-        HIP_TRY(launch_zero(sc->moments.p, sc->moments.bytes, s));
+    if (!sc->arrived_zeroed) {
+        PCR_TRY(sc->arrived.ensure(sizeof(unsigned), dev, s));
+        HIP_TRY(launch_zero(sc->arrived.p, sc->arrived.bytes, s));
+        sc->arrived_zeroed = true;
     }
     PCR_TRY(sc->host.ensure(kHostSlots));
     return PCR_OK;
@@ -545,8 +549,9 @@ pcr_status Evaluator::enqueue_eval(const double* w)
     // then publishes this evaluation's sequence number there
     double* mom = sc->host.d;
     unsigned long long* done = (unsigned long long*)(sc->host.d + kDoneSlot);
-    unsigned* arrived = (unsigned*)((double*)sc->moments.p + kMaxMoments);
+    unsigned* arrived = (unsigned*)sc->arrived.p;
     const unsigned long long seq = ++sc->seq;
+    sc->settled = false;
     RayGeom gc = rgc, g1 = rg;
     int vbox[6];
     const int* box = nullptr;
@@ -613,6 +618,7 @@ void Evaluator::collect(Moments& out) const
     out.samples = sc->host.p[n_moments(kc)];
     out.M = (double)M;
     out.K = model->K;
+    sc->settled = true;
 }
 
 pcr_status Evaluator::eval_sync(const double* w, Moments& out)
@@ -628,6 +634,7 @@ pcr_status Evaluator::grad_adjoint(const double* w, double a, double b, double* 
     double w_eff[8];
     effective_w(*model, w, w_eff);
     const int K = model->K;
+    sc->settled = false;
     {
         PROF(BACKPROJ, s);
         HIP_TRY(launch_backproject(compute, *grid, rg, nullptr, sc->p.p, y, a, b, 2.0, sc->acc1.p, s));
@@ -640,10 +647,11 @@ pcr_status Evaluator::grad_adjoint(const double* w, double a, double b, double* 
     {
         PROF(REDUCE, s);
         HIP_TRY(launch_reduce_publish((const double*)sc->partials.p, contract_blocks(*grid), K, sc->host.d,
-                                      (unsigned*)((double*)sc->moments.p + kMaxMoments),
+                                      (unsigned*)sc->arrived.p,
                                       (unsigned long long*)(sc->host.d + kDoneSlot), ++sc->seq, s));
     }
     PCR_TRY(wait_published());
+    sc->settled = true;
     for (int k = 0; k < K; ++k) grad[k] = sc->host.p[k];
     return PCR_OK;
 }

@@ -147,21 +147,26 @@ struct Moments {
 
 // Device scratch of one solve in flight: the zero-padded fused image, the
 // single-channel image, backprojection and projection buffers of the
-// adjoint mode, reduction partials, moments and pinned host staging.
+// adjoint mode, reduction partials, the word in which the workgroups of a
+// final sum count themselves (zero between launches) and pinned host staging.
 struct Scratch {
     int device = -1;
     PadLayout Lc{}, L1{};
     PadLayout volc_layout{};   // layout whose zero borders volc holds
-    bool volc_zeroed = false;
+    bool volc_zeroed = false, vol1_zeroed = false, arrived_zeroed = false;
+    // Whether all that was enqueued with this scratch is known to have run (its
+    // sums came out).  Where it is not, as after an evaluation on a capturing
+    // stream, prepare() clears again what has to hold zeros.
+    bool settled = false;
     size_t volc_floor = 0;     // allocate volc at least this large (a serving slot
                                // sized once for every admitted stream)
-    DevBuf volc, vol1, acc1, p, partials, moments;
+    DevBuf volc, vol1, acc1, p, partials, arrived;
     HostBuf host;
     unsigned long long seq = 0;   // sequence number of the last evaluation
     void release();
     size_t device_bytes() const
     {
-        return volc.bytes + vol1.bytes + acc1.bytes + p.bytes + partials.bytes + moments.bytes;
+        return volc.bytes + vol1.bytes + acc1.bytes + p.bytes + partials.bytes + arrived.bytes;
     }
 };
 

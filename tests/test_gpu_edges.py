@@ -115,3 +115,56 @@ def test_projection_of_the_longest_grid(nz, noalloc):
     vol = torch.tensor(x, dtype=torch.float64, device=DEV)
     (L.forward_project_noalloc if noalloc else L.forward_project)(g, G, vol, out)
     assert rel_l2(out.cpu().numpy(), oracle.project(g, G, x)) <= 1e-12
+
+
+def _hip():
+    """The HIP runtime that this process has loaded."""
+    for line in open("/proc/self/maps"):
+        if "libamdhip64" in line:
+            return C.CDLL(line.split()[-1])
+    raise RuntimeError("no HIP runtime loaded")
+
+
+@pytest.mark.parametrize("mode", ["fused", "adjoint"])
+def test_evaluation_after_one_that_a_capture_refused(mode):
+    """An evaluation waits for its sums, so on a capturing stream it fails, and
+    what it enqueued there never runs.  The next one on the same context must
+    not count on it: its result is a fresh context's."""
+    L = _lib()
+    hip = _hip()
+    grad_mode = L.GRAD_FUSED if mode == "fused" else L.GRAD_ADJOINT
+    g = S.Grid((24, 20, 16), (3.0, 3.0, 3.0))
+    G = S.Geom(math.radians(35.0), 33, 40, 2.7, 2.0, 1.5)
+    f = torch.tensor(S.phantom(g, seed=8), dtype=torch.float32, device=DEV)
+    z = np.indices(g.shape) / 7.0
+    mean = torch.tensor(np.stack([2.0 * np.sin(z[a] + a) for a in range(3)]), dtype=torch.float32, device=DEV)
+    U = torch.tensor(np.stack([np.sin(z[a] * 1.3) for a in range(3)])[None], dtype=torch.float32, device=DEV)
+    y = torch.ones((40, 33), device=DEV)
+    model = L.DeviceModel(mean, U)
+    ctx = L.Context(g, model, f)
+    want = ctx.cost_grad(y, G, [0.4], 0.9, 0.01, mode=grad_mode)
+    ctx.close()
+    # freed device memory that does not hold zeros
+    sizes = [256] * 64 + [1 << 15] * 8 + [1 << 17] * 8
+    p = [C.c_void_p() for _ in sizes]
+    for q, n in zip(p, sizes):
+        assert hip.hipMalloc(C.byref(q), C.c_size_t(n)) == 0
+        assert hip.hipMemset(q, 0xA5, C.c_size_t(n)) == 0
+    torch.cuda.synchronize()
+    for q in p:
+        assert hip.hipFree(q) == 0
+    ctx = L.Context(g, model, f)
+    small = S.Geom(0.5, 33, 40, 2.7, 2.0, 1e-6)
+    with pytest.raises(L.PCRError):   # refused, once the image's support is known
+        ctx.cost_grad(y, small, [0.4], 0.9, 0.01, mode=grad_mode)
+    s = torch.cuda.Stream()
+    assert hip.hipStreamBeginCapture(C.c_void_p(s.cuda_stream), 2) == 0   # relaxed
+    with pytest.raises(L.PCRError):
+        ctx.cost_grad(y, G, [0.4], 0.9, 0.01, mode=grad_mode, stream=s)
+    graph = C.c_void_p()
+    hip.hipStreamEndCapture(C.c_void_p(s.cuda_stream), C.byref(graph))   # (invalid by now)
+    hip.hipGetLastError()
+    for _ in range(3):
+        got = ctx.cost_grad(y, G, [0.4], 0.9, 0.01, mode=grad_mode)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1])
+    ctx.close()
