@@ -223,11 +223,12 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom,
  * a per-thread allocation.  The array is part of the library's code object:
  * each GPU the library runs on holds it until the process ends; its device
  * address is looked up once per GPU on the first call there.  A grid whose
- * padded copy exceeds the array returns PCR_EINVAL before any launch.  Every
- * call on one GPU shares the array (and refills it): calls that overlap on
- * one GPU (other host threads, or streams not ordered with each
- * other) race and give undefined projections.  Not timed by the kernel
- * profiler (pcr_profile_enable), which records events. */
+ * padded copy exceeds the array returns PCR_EINVAL before any launch.  All
+ * calls on one GPU that march the copy (FP64, coarse detectors and shared
+ * memory, as above) share the array and refill it: two of them that overlap
+ * (other host threads, or streams not ordered with each other) race and give
+ * undefined projections.  Not timed by the kernel profiler
+ * (pcr_profile_enable), which records events. */
 #define PCR_NOALLOC_SCRATCH_BYTES ((size_t)64 << 20)
 pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geom,
                                        pcr_dtype compute, const void* vol_dev, void* proj_dev,

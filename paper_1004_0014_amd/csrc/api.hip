@@ -882,16 +882,18 @@ pcr_status pcr_forward_project_noalloc(const pcr_grid* grid, const pcr_geom* geo
                     "the fixed scratch array",
                     grid->n[0], grid->n[1], grid->n[2], bytes, (size_t)PCR_NOALLOC_SCRATCH_BYTES);
     hipStream_t s = (hipStream_t)stream;
+    // (on every call, so that the first one on a GPU looks the address up
+    // whether or not it needs the array)
+    int dev;
+    PCR_TRY(current_device(&dev));
+    void* pad = nullptr;
+    PCR_TRY(scratch_on_device(dev, &pad));
     const RayGeom rg = make_ray_geom(*grid, *geom);
     const MarchShape ms = choose_march_shape(rg, compute, true);
     if (reads_volume(compute, rg, L, vol_dev, proj_dev)) {
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;
     }
-    int dev;
-    PCR_TRY(current_device(&dev));
-    void* pad = nullptr;
-    PCR_TRY(scratch_on_device(dev, &pad));
     HIP_TRY(launch_pad(compute, L, vol_dev, pad, s));
     HIP_TRY(launch_march(compute, L, 1, rg, ms, pad, nullptr, proj_dev, nullptr, nullptr, nullptr, nullptr, 0,
                          s));

@@ -168,3 +168,46 @@ def test_evaluation_after_one_that_a_capture_refused(mode):
         got = ctx.cost_grad(y, G, [0.4], 0.9, 0.01, mode=grad_mode)
         assert got[0] == want[0] and np.array_equal(got[1], want[1])
     ctx.close()
+
+
+# Captured projections, in a process of their own (the library keeps what the
+# first calls of a process and of a thread set up).
+_CAPTURED = """
+import torch
+from paper_1004_0014_amd import _lib as L, synth as S
+g = S.Grid((40, 36, 28), (2.0, 2.0, 2.0))
+fine, coarse = S.Geom(0.4, 72, 52, 1.5, 1.5, 1.0), S.Geom(0.4, 9, 7, 30.0, 30.0, 1.0)
+x = torch.tensor(S.phantom(g, seed=2), dtype=torch.%s, device="cuda")
+xf, pf = x.float(), torch.empty((52, 72), device="cuda")
+G = %s
+p = torch.full((G.nv, G.nu), float("nan"), dtype=x.dtype, device="cuda")
+%s
+s = torch.cuda.Stream()
+s.wait_stream(torch.cuda.current_stream())
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=s):
+    %s(g, G, x, p, stream=s)
+want = L.forward_project(g, G, x)
+assert want.abs().max() > 0
+for k in range(3):
+    p.fill_(float("nan"))
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(p, want), k
+print("replays equal")
+"""
+
+
+def _captured(*parts):
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _CAPTURED % parts], cwd=root, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "replays equal" in r.stdout, r.stdout + r.stderr
+
+
+def test_first_padded_noalloc_projection_under_capture():
+    """A process whose first allocation-free projection needs no padded copy
+    and whose second, which does, is captured."""
+    _captured("float64", "fine", "L.forward_project_noalloc(g, fine, xf, pf)", "L.forward_project_noalloc")
