@@ -171,7 +171,7 @@ pcr_status check_opts(const pcr_solve_opts* o)
 pcr_status DevBuf::ensure(size_t need, int dev, hipStream_t s)
 {
     need = (need + 255) & ~(size_t)255;
-    if (p && bytes >= need && device == dev) return PCR_OK;
+    if (holds(need, dev)) return PCR_OK;
     if (p) {
         HIP_TRY(hipStreamSynchronize(s));
         HIP_TRY(hipFree(p));
@@ -662,15 +662,41 @@ pcr_status Evaluator::grad_adjoint(const double* w, double a, double b, double* 
 namespace {
 struct TlsScratch {
     DevBuf pad;
+    bool in_graph = false;      // a captured call's graph may use `pad`
+    std::vector<DevBuf> kept;   // outgrown ones that graphs may use
     HostBuf host;   // up to 8 results, then the sequence number of published ones
     unsigned long long seq = 0;
     ~TlsScratch()
     {
         pad.release();
+        for (DevBuf& b : kept) b.release();
         host.release();
     }
 };
 thread_local TlsScratch tls;
+
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
+// The thread's scratch, of at least `need` bytes.  A buffer that a captured
+// call left to its graph stays allocated when it is outgrown.
+pcr_status pad_room(size_t need, int dev, hipStream_t s)
+{
+    if (!tls.pad.holds(need, dev) && tls.in_graph) {
+        try {
+            tls.kept.push_back(tls.pad);
+        } catch (...) {
+            return fail(PCR_ENOMEM, "host allocation failed");
+        }
+        tls.pad = DevBuf{};
+        tls.in_graph = false;
+    }
+    return tls.pad.ensure(need, dev, s);
+}
 
 pcr_status current_device(int* dev)
 {
@@ -854,7 +880,8 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     }
     int dev;
     PCR_TRY(current_device(&dev));
-    PCR_TRY(tls.pad.ensure(L.cells() * dtype_size(compute), dev, s));
+    PCR_TRY(pad_room(L.cells() * dtype_size(compute), dev, s));
+    if (capturing(s)) tls.in_graph = true;
     {
         PROF(PAD, s);
         HIP_TRY(launch_pad(compute, L, vol_dev, tls.pad.p, s));
@@ -928,7 +955,7 @@ pcr_status pcr_warp_contract(const pcr_grid* grid, const pcr_model* model, pcr_d
     int dev;
     PCR_TRY(current_device(&dev));
     const int nb = contract_blocks(*grid);
-    PCR_TRY(tls.pad.ensure((size_t)nb * 8 * sizeof(double) + 8 * sizeof(double), dev, s));
+    PCR_TRY(pad_room((size_t)nb * 8 * sizeof(double) + 8 * sizeof(double), dev, s));
     PCR_TRY(tls.host.ensure(8));
     double w_eff[8];
     effective_w(*model, w_host, w_eff);

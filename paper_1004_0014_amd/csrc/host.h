@@ -88,6 +88,7 @@ struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
     int device = -1;
+    bool holds(size_t need, int dev) const { return p && bytes >= need && device == dev; }
     pcr_status ensure(size_t need, int dev, hipStream_t s);
     void release();
 };

@@ -189,6 +189,7 @@ with torch.cuda.graph(graph, stream=s):
     %s(g, G, x, p, stream=s)
 want = L.forward_project(g, G, x)
 assert want.abs().max() > 0
+%s
 for k in range(3):
     p.fill_(float("nan"))
     graph.replay()
@@ -198,12 +199,12 @@ print("replays equal")
 """
 
 
-def _captured(*parts):
+def _captured(dtype, geom, before, call, after=""):
     import os
     import subprocess
     import sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    r = subprocess.run([sys.executable, "-c", _CAPTURED % parts], cwd=root, capture_output=True, text=True, timeout=100)
+    r = subprocess.run([sys.executable, "-c", _CAPTURED % (dtype, geom, before, call, after)], cwd=root, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "replays equal" in r.stdout, r.stdout + r.stderr
 
 
@@ -211,3 +212,14 @@ def test_first_padded_noalloc_projection_under_capture():
     """A process whose first allocation-free projection needs no padded copy
     and whose second, which does, is captured."""
     _captured("float64", "fine", "L.forward_project_noalloc(g, fine, xf, pf)", "L.forward_project_noalloc")
+
+
+def test_graph_keeps_the_scratch_that_a_later_call_outgrows():
+    """A captured projection, then one of a larger grid, which needs a larger
+    copy: the graph's replays still have theirs."""
+    _captured("float64", "fine", "L.forward_project(g, G, x)", "L.forward_project", """
+big = S.Grid((60, 50, 40), (2.0, 2.0, 2.0))
+y = torch.tensor(S.phantom(big, seed=3), dtype=torch.float64, device="cuda")
+q = L.forward_project(big, G, y)
+junk = [torch.full((40 * 36 * 28,), 7.0, dtype=torch.float64, device="cuda") for _ in range(64)]
+""")
