@@ -698,6 +698,19 @@ pcr_status pad_room(size_t need, int dev, hipStream_t s)
     return tls.pad.ensure(need, dev, s);
 }
 
+// The same for a later call on `s`, where it can be had at once and no capture
+// is in the way (the relaxed mode keeps the allocation out of other streams').
+void keep_room(size_t need, int dev, hipStream_t s)
+{
+    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+    if (tls.pad.holds(need, dev) || capturing(s)) return;
+    if (hipThreadExchangeStreamCaptureMode(&m) == hipSuccess) {
+        (void)pad_room(need, dev, s);
+        (void)hipThreadExchangeStreamCaptureMode(&m);
+    }
+    (void)hipGetLastError();
+}
+
 pcr_status current_device(int* dev)
 {
     HIP_TRY(hipGetDevice(dev));
@@ -873,14 +886,18 @@ pcr_status pcr_forward_project(const pcr_grid* grid, const pcr_geom* geom, pcr_d
     const PadLayout L = make_pad(*grid, 1);
     const RayGeom rg = make_ray_geom(*grid, *geom);
     const MarchShape ms = choose_march_shape(rg, compute, true);
+    int dev;
+    PCR_TRY(current_device(&dev));
+    const size_t bytes = L.cells() * dtype_size(compute);
     if (reads_volume(compute, rg, L, vol_dev, proj_dev)) {
+        // (the rule depends on the angle: a call at another angle that
+        // marches the copy may be captured, and cannot allocate then)
+        keep_room(bytes, dev, s);
         PROF(MARCH, s);
         HIP_TRY(launch_project_f32(L, rg, ms, vol_dev, proj_dev, s));
         return PCR_OK;
     }
-    int dev;
-    PCR_TRY(current_device(&dev));
-    PCR_TRY(pad_room(L.cells() * dtype_size(compute), dev, s));
+    PCR_TRY(pad_room(bytes, dev, s));
     if (capturing(s)) tls.in_graph = true;
     {
         PROF(PAD, s);

@@ -223,3 +223,11 @@ y = torch.tensor(S.phantom(big, seed=3), dtype=torch.float64, device="cuda")
 q = L.forward_project(big, G, y)
 junk = [torch.full((40 * 36 * 28,), 7.0, dtype=torch.float64, device="cuda") for _ in range(64)]
 """)
+
+
+@pytest.mark.parametrize("before", ["", "L.forward_project(S.Grid((8, 8, 8), (2.0, 2.0, 2.0)), coarse, x[:8, :8, :8].contiguous())"])
+def test_padded_projection_captured_after_one_that_is_not(before):
+    """A projection that needs no padded copy, then, captured, one of the same
+    grid that does, in a thread with no scratch or a smaller one: its room is
+    there, as a capture cannot allocate it."""
+    _captured("float32", "coarse", before + "\nL.forward_project(g, fine, x, pf)", "L.forward_project")
