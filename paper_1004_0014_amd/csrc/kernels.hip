@@ -2833,18 +2833,39 @@ hipError_t launch_backproject(pcr_dtype compute, const pcr_grid& g, const RayGeo
         diag += e * e;
     }
     const bool many = std::sqrt(diag) * rg.inv_dt + 2.0 > (double)kBpReach;
+    // 2 x 2 columns make four times the blocks, each column with 64 lanes for
+    // its rays (51x57x41 voxels, 623x462 pixels: 4.4 -> 0.54 ms; 48x48x32,
+    // 128x96: 38 -> 24 us; 80x80x40, 256x192: 92 -> 80 us).  From 1024 bricks of
+    // 4 x 4 on (64^3, equal) the rays staged once per brick count more: 4096
+    // bricks 99 against 165 us.  Below, what counts is whether the rays keep
+    // the lanes busy for longer than the blocks' own cost (clearing and summing
+    // the runs): the samples a column takes, its rays where the volume is
+    // nearest the source times the samples of one, against the blocks that each
+    // CU goes through (its LDS holds five in FP32, two in FP64).  10x102x110
+    // voxels under 13x1 pixels: 12 against 22 us, in FP64 12 against 32.  The
+    // line is the best over 450 random calls up to 1.2 M voxels and 0.25 M
+    // pixels: in all 2.4 % (FP32) and 2.6 % (FP64) above the better shape of
+    // each (2 x 2 wherever there are under 1024 bricks: 7 and 12 %).
+    double depth = a0;
+    for (int ax = 0; ax < 3; ++ax) {
+        const double half = 0.5 * rg.lim[ax] * rg.sp[ax];
+        depth += (half - 0.5 * rg.sp[ax]) * n[ax] - half * std::fabs(n[ax]);
+    }
+    depth = std::max(depth, 0.02 * sdd);
+    const int bx = 1 - A.ax;
+    const double wide = 2.0 * rg.sp[bx] * std::fabs(eu[bx]) + 17.0 * rg.sp[A.ax] * std::fabs(eu[A.ax]);
+    const double rays = std::min((double)rg.nu, wide * sdd / (depth * rg.du)) *
+                        std::min((double)rg.nv, 2.0 * rg.sp[2] * sdd / (depth * rg.dv));
+    const double samples = std::min(17.0 * rg.sp[A.ax] / std::max(std::fabs(n[A.ax]), 1e-9),
+                                    2.0 * rg.sp[bx] / std::max(std::fabs(n[bx]), 1e-9)) * rg.inv_dt;
+    const double resident = compute == PCR_F32 ? 1280.0 : 512.0;
+    const bool small = !many && blocks < 1024 && rays * samples * resident > 512.0 * (double)bricks(2);
+    blocks = bricks(small ? 2 : 4);
 #define PCR_BP(CB, MODE) \
     k_backproject_columns<R, CB, MODE><<<(unsigned)blocks, 256, 0, s>>>(A, (const R*)resid, (const R*)p, (const R*)y, (R*)out)
     if (many) {
         PCR_DISPATCH_R(compute, R, PCR_BP(4, kMany));
-    } else if (blocks < 1024) {
-        // fewer than the chip holds at once (five per CU): 2 x 2 columns make
-        // four times the blocks, each column with 64 lanes for its rays
-        // (51x57x41 voxels, 623x462 pixels: 4.4 -> 0.54 ms; 48x48x32, 128x96:
-        // 38 -> 24 us; 80x80x40, 256x192: 92 -> 80 us).  At 1024 blocks (64^3)
-        // the two are equal; beyond, the rays staged once per brick count: 4096
-        // blocks 99 against 165 us.
-        blocks = bricks(2);
+    } else if (small) {
         PCR_DISPATCH_R(compute, R, if (mode == kPairs) PCR_BP(2, kPairs); else PCR_BP(2, kSingles));
     } else {
         PCR_DISPATCH_R(compute, R, if (mode == kPairs) PCR_BP(4, kPairs); else PCR_BP(4, kSingles));

@@ -231,3 +231,22 @@ def test_padded_projection_captured_after_one_that_is_not(before):
     grid that does, in a thread with no scratch or a smaller one: its room is
     there, as a capture cannot allocate it."""
     _captured("float32", "coarse", before + "\nL.forward_project(g, fine, x, pf)", "L.forward_project")
+
+
+@pytest.mark.parametrize("n,nu,nv,du", [
+    ((40, 33, 21), 5, 4, 30.0),       # few bricks under few rays: 4 x 4 columns
+    ((40, 33, 21), 40, 33, 4.0),      # near the rule's line, on one side in FP32
+    ((40, 33, 21), 90, 70, 1.7),      # and on the other
+    ((10, 102, 110), 13, 1, 9.0),     # no ray for most bricks
+])
+@pytest.mark.parametrize("ang", [20.0, 110.0])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_backprojection_by_the_rays_of_a_column(n, nu, nv, du, ang, dtype):
+    """Few bricks with few and many rays, which decide the brick's shape: the
+    backprojection parity bounds."""
+    L = _lib()
+    g = S.Grid(n, (2.0, 2.0, 2.5))
+    G = S.Geom(math.radians(ang), nu, nv, du, du, 1.0, off_u=0.3)
+    r_t, r = rounded(S.seeded(4, (nv, nu)), dtype)
+    bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
+    assert rel_l2(bp, oracle.backproject(g, G, r)) <= (1e-5 if dtype == torch.float32 else 1e-12)
