@@ -250,3 +250,21 @@ def test_backprojection_by_the_rays_of_a_column(n, nu, nv, du, ang, dtype):
     r_t, r = rounded(S.seeded(4, (nv, nu)), dtype)
     bp = L.backproject_residual(g, G, r_t.to(DEV)).cpu().numpy()
     assert rel_l2(bp, oracle.backproject(g, G, r)) <= (1e-5 if dtype == torch.float32 else 1e-12)
+
+
+@pytest.mark.parametrize("K", [1, 2, 3, 4, 5, 6, 8])
+@pytest.mark.parametrize("storage", [torch.float32, torch.bfloat16])
+def test_localisation_by_field_count(K, storage):
+    """Localisation with every count of fields an instance takes: FP64 on both
+    sides, so the points agree within the fixed point's tolerance of 1e-9 mm."""
+    L = _lib()
+    g = S.Grid((14, 11, 9), (2.0, 2.5, 3.0))
+    z = np.indices(g.shape) / 9.0
+    mean_t, mean = rounded(np.stack([2.0 * np.sin(z[a] + a) for a in range(3)]), storage)
+    U_t, U = rounded(np.stack([np.stack([np.cos(z[(a + k) % 3] * (1 + 0.2 * k) + a) for a in range(3)]) for k in range(K)]), storage)
+    w = 0.6 * np.random.default_rng(K).uniform(-1.0, 1.0, K) / K
+    p = (3.1, -2.2, 1.7)
+    got, st, it = L.localize_tumor(g, L.DeviceModel(mean_t.to(DEV), U_t.to(DEV)), list(w), p, tol=1e-9)
+    want = oracle.localize(g, mean, U, w, p, tol=1e-9)[0]
+    assert st == L.PCR_OK and it > 2
+    np.testing.assert_allclose(got, want, rtol=0, atol=2e-9)
