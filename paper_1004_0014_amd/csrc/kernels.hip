@@ -632,9 +632,9 @@ __global__ void __launch_bounds__(256) k_zero4(uint32_t* __restrict__ p, size_t 
 // ---------------------------------------------------------- ray march ----
 template <typename R>
 struct RaySeg {
-    R q0[3];         // index-space point of the segment's first sample
+    R q0[3];         // index-space point of sample 0
     R dq[3];         // index-space step per sample
-    int count;       // samples in the segment
+    int first, end;  // the segment's samples
 };
 
 // One direction of the slab tests along a ray: the coordinate o + t d,
@@ -746,8 +746,10 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
     }
     if (!(L2 > 0.0)) return r;
     const double iL = rsq64(L2);
-    // the length and its quotient by dt corrected once more, so that a
-    // sample exactly on the detector is kept or dropped as by sqrt and /
+    // the length, the quotients by it and its quotient by dt corrected once
+    // more: correctly rounded, as by sqrt and /, so that a sample exactly on
+    // the detector is kept or dropped as by those, and positions far along a
+    // ray are as exact
     double L = L2 * iL;
     L = fma(0.5 * iL, fma(-L, L, L2), L);
     double nl = L * g.inv_dt;
@@ -756,7 +758,8 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
     bool hit = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double d = D[a] * iL;
+        double d = D[a] * iL;
+        d = fma(iL, fma(-d, L, D[a]), d);
         r.dq[a] = d;
         if (fabs(d) > 1e-280) {
             const double i = rcp64(d);
@@ -779,15 +782,22 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
     return r;
 }
 
-// The ray's range split into `seg` equal segments: segment `sid`.
+// The ray's range split into `seg` equal segments: segment `sid`.  Positions
+// are formed from the start of a quarter of the ray at most: more segments
+// than four split a quarter's samples, and share its start, so that a sample
+// lies at the same point however many threads a ray has (with starts of their
+// own, sixteen segments had 3 % more error against 80-bit projections).
 template <typename R>
 __device__ __forceinline__ RaySeg<R> ray_segment(const RayGeom& g, int iu, int iv, int seg, int sid)
 {
     RaySeg<R> r;
     const RayRange rr = ray_range(g, iu, iv);
     const long cnt = rr.n1 >= rr.n0 ? (long)rr.n1 - rr.n0 + 1 : 0;
-    long m0 = cnt * sid / seg, m1 = cnt * (sid + 1) / seg;
-    r.count = (int)(m1 - m0);
+    // (seg is a power of two: np parts of `per` segments)
+    const int np = min(__builtin_ctz(seg), 2), per = __builtin_ctz(seg) - np, p = sid >> per, c = sid & ((1 << per) - 1);
+    const long m0 = cnt * p >> np, n = (cnt * (p + 1) >> np) - m0;
+    r.first = (int)(n * c >> per);
+    r.end = (int)(n * (c + 1) >> per);
     double t0 = (double)(rr.n0 + m0) * g.dt;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -826,7 +836,7 @@ __global__ void __launch_bounds__(256) k_march(RayGeom g, MarchShape ms, int til
     int nsamp = 0;
     if (valid) {
         RaySeg<R> rs = ray_segment<R>(g, iu, iv, ms.seg, sid);
-        nsamp = rs.count;
+        nsamp = rs.end - rs.first;
         const long pxy = (long)px * py;
         const Chan<R, C>* base = vol + (1 + px + pxy);   // cell of voxel (0,0,0)
         // (two samples' loads in flight, for one channel: FP64 256x256x100 onto
@@ -834,7 +844,7 @@ __global__ void __launch_bounds__(256) k_march(RayGeom g, MarchShape ms, int til
         // us; four take the registers: 205 / 249 / 188)
         constexpr int kUnroll = C == 1 ? 2 : 1;
 #pragma unroll kUnroll
-        for (int m = 0; m < rs.count; ++m) {
+        for (int m = rs.first; m < rs.end; ++m) {
             R fm = (R)m;
             R qx = clampv(fma(fm, rs.dq[0], rs.q0[0]), (R)-1, (R)fnx);
             R qy = clampv(fma(fm, rs.dq[1], rs.q0[1]), (R)-1, (R)fny);
