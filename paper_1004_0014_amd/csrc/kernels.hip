@@ -730,6 +730,8 @@ struct RayRange {
     double dq[3];
 };
 
+// R: the precision in which the ray's positions are formed.
+template <typename R>
 __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
 {
     RayRange r;
@@ -746,10 +748,10 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
     }
     if (!(L2 > 0.0)) return r;
     const double iL = rsq64(L2);
-    // the length, the quotients by it and its quotient by dt corrected once
-    // more: correctly rounded, as by sqrt and /, so that a sample exactly on
-    // the detector is kept or dropped as by those, and positions far along a
-    // ray are as exact
+    // the length and its quotient by dt (and in FP64 the quotients by it)
+    // corrected once more: correctly rounded, as by sqrt and /, so that a
+    // sample exactly on the detector is kept or dropped as by those, and FP64
+    // positions far along a ray are as exact
     double L = L2 * iL;
     L = fma(0.5 * iL, fma(-L, L, L2), L);
     double nl = L * g.inv_dt;
@@ -759,7 +761,7 @@ __device__ __forceinline__ RayRange ray_range(const RayGeom& g, int iu, int iv)
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         double d = D[a] * iL;
-        d = fma(iL, fma(-d, L, D[a]), d);
+        if constexpr (std::is_same<R, double>::value) d = fma(iL, fma(-d, L, D[a]), d);
         r.dq[a] = d;
         if (fabs(d) > 1e-280) {
             const double i = rcp64(d);
@@ -791,7 +793,7 @@ template <typename R>
 __device__ __forceinline__ RaySeg<R> ray_segment(const RayGeom& g, int iu, int iv, int seg, int sid)
 {
     RaySeg<R> r;
-    const RayRange rr = ray_range(g, iu, iv);
+    const RayRange rr = ray_range<R>(g, iu, iv);
     const long cnt = rr.n1 >= rr.n0 ? (long)rr.n1 - rr.n0 + 1 : 0;
     // (seg is a power of two: np parts of `per` segments)
     const int np = min(__builtin_ctz(seg), 2), per = __builtin_ctz(seg) - np, p = sid >> per, c = sid & ((1 << per) - 1);
@@ -1049,14 +1051,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
         // the segment-0 waves set up the block's rays, the others read them
         RayRange* rbuf = (RayRange*)smem;
         if (sid == 0) {
-            if (valid) rr = ray_range(g, iu, iv);
+            if (valid) rr = ray_range<float>(g, iu, iv);
             rbuf[rloc] = rr;
         }
         __syncthreads();
         rr = rbuf[rloc];
         __syncthreads();   // before the buffer is reused for the partial sums
     } else if (valid) {
-        rr = ray_range(g, iu, iv);
+        rr = ray_range<float>(g, iu, iv);
     }
     int N0 = rr.n1 >= rr.n0 ? rr.n0 : INT_MAX, N1 = rr.n1 >= rr.n0 ? rr.n1 : INT_MIN;
     N0 = __builtin_amdgcn_readfirstlane(__ockl_wfred_min_i32(N0));
@@ -1331,14 +1333,14 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ma
     if (A.ms.seg > 1) {
         RayRange* rbuf = (RayRange*)smem;
         if (sid == 0) {
-            if (valid) rr = ray_range(g, iu, iv);
+            if (valid) rr = ray_range<float>(g, iu, iv);
             rbuf[rloc] = rr;
         }
         __syncthreads();
         rr = rbuf[rloc];
         __syncthreads();   // before the buffer is reused for staging
     } else if (valid) {
-        rr = ray_range(g, iu, iv);
+        rr = ray_range<float>(g, iu, iv);
     }
     int N0 = rr.n1 >= rr.n0 ? rr.n0 : INT_MAX, N1 = rr.n1 >= rr.n0 ? rr.n1 : INT_MIN;
     N0 = __builtin_amdgcn_readfirstlane(__ockl_wfred_min_i32(N0));
