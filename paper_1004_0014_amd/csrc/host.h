@@ -35,6 +35,7 @@ pcr_status fail(pcr_status code, const char* fmt, ...);
 
 // ----------------------------------------------------------- profiler ----
 namespace prof {
+// (UNPAD: no kernel any more; it keeps the bits of the kinds after it)
 enum Id { WARP, MARCH, REDUCE, BACKPROJ, CONTRACT, LOCALIZE, ZERO, PAD, UNPAD, COMPOSE, WARP_PLAIN,
           WARP_ADJ, PCA_GRAM, PCA_FIELDS, NKERN };
 // Brackets one launch with HIP events on `s` while profiling is enabled.

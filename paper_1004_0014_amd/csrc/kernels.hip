@@ -6,7 +6,8 @@
 // return the cost and its gradient in w.
 //
 //  * Voxel passes (compose, warp, contraction) stream HBM: one thread per
-//    voxel, x-contiguous lanes, structure-of-arrays fields.
+//    voxel (composition: per four values), x-contiguous lanes,
+//    structure-of-arrays fields.
 //  * The ray march gathers from a zero-padded, channel-interleaved copy of
 //    the warped image that stays resident in L2/MALL; each lane marches one
 //    ray (or one segment of one) so a wave's taps fall in a compact 3-D
@@ -533,9 +534,10 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
 // 49 us, 6 TB/s with part of the model in the Infinity Cache; a BF16 model
 // moves fewer bytes a load and was bound by the chain of waits until all of
 // a voxel's loads went out together (load_fields, sample_f0): K = 4 at
-// 256x256x128 102 -> 69 us, K = 5 at 512x512x160 520 -> 370 us (1.5 GB).  (Ordering the runs by XCD, as the y-fastest tiles are, was 2-4 %
-// slower here: in dispatch order the XCDs work on neighbouring rows at the
-// same time and share their f0 taps through the Infinity Cache.)
+// 256x256x128 102 -> 69 us, K = 5 at 512x512x160 520 -> 370 us (1.5 GB).
+// (Ordering the runs by XCD, as the y-fastest tiles are, was 2-4 % slower here:
+// in dispatch order the XCDs work on neighbouring rows at the same time and
+// share their f0 taps through the Infinity Cache.)
 template <typename R, typename S, typename F, int C, bool TAN, bool H, int KM>
 __global__ void __launch_bounds__(256) k_warp_fused(const F* __restrict__ f0,
                                                     const S* __restrict__ mean,
@@ -923,7 +925,9 @@ __global__ void __launch_bounds__(256) k_march(RayGeom g, MarchShape ms, int til
 // rows (xcd_tile) the tiles go from the middle column outwards.  The rays
 // through the middle of the volume are the longest, and a block takes about
 // half the launch's time: with the long blocks first the short ones fill in
-// at the end.
+// at the end (1833 -> 1805 us a solve at 256x256x100).  With a shifted detector
+// or isocentre the middle column need not be the longest; the order then
+// gains less, and the sums are the same.
 __device__ __forceinline__ void march_tile(int b, int nb, int tiles_u, int& tu, int& tv)
 {
     const int q = nb >> 3, rem = nb & 7, x = b & 7;
@@ -1012,14 +1016,14 @@ struct MarchArgs {
     float ihs[8];          // FP16 cells: 1 / channel scale
 };
 
-// The march gathering its taps through the vector L1.  The library launches
-// it for FP16 cells (H), where the VALU binds; FP32 cells go to the
-// LDS-staged k_march_lds below, which takes the same samples in the same
-// order and gives bitwise the same sums as this kernel's FP32 form.
-template <int C, bool H>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4 ? 8 : 1))) k_march_f32(MarchArgs A)
+// The march of FP16 cells, gathering its taps through the vector L1 (where the
+// VALU binds: FP32 cells, which the L1 bound, go to the LDS-staged k_march_lds
+// below).  It got neither the staging nor the tile order of that kernel: at
+// 30 deg and K = 3 it takes 149 us, the staged march of FP32 cells 127.
+template <int C>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4 ? 8 : 1))) k_march_f16(MarchArgs A)
 {
-    constexpr int CB = (H ? 2 : 4) * C;   // bytes per cell
+    constexpr int CB = 2 * C;   // bytes per cell
     const RayGeom& g = A.g;
     const int rpb = 256 / A.ms.seg;
     const int rloc = threadIdx.x % rpb, sid = threadIdx.x / rpb;
@@ -1076,19 +1080,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
         const float dqx = (float)(g.dt * rr.dq[0]), dqy = (float)(g.dt * rr.dq[1]),
                     dqz = (float)(g.dt * rr.dq[2]);
         const int YS = A.ys, ZS = A.zs, YZ = A.ys + A.zs, PY = A.py;
-        // A step is half a voxel or less, so consecutive samples of a lane
-        // often fall in the same cell: with FP32 cells (bound by the L1) the
-        // lane keeps its last 8 cells and loads only when the cell changes
-        // (lanes that reuse are masked out of the load and cost no L1
-        // bandwidth).  FP16 cells (bound by the VALU) always load: there the
-        // branch costs more than the bandwidth it saves (measured).
-        CellPair<C> p00, p10, p01, p11;
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            p00.a[c] = p00.b[c] = p10.a[c] = p10.b[c] = 0.f;
-            p01.a[c] = p01.b[c] = p11.a[c] = p11.b[c] = 0.f;
-        }
-        int last = -1;
+        // (a lane loads at every sample, though consecutive ones often fall in
+        // the same cell: a branch would cost more than the bandwidth it saves)
         for (int n = na; n < nb; ++n) {
             if (n < rr.n0 || n > rr.n1) continue;
             ++nsamp;
@@ -1103,22 +1096,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
             // the image size < 2^31 (checked at launch), so the 24-bit
             // products are exact
             const int voff = ix * CB + (int)__umul24(__umul24(iz, PY) + iy, YS);
-            if (H || voff != last) {
-                last = voff;
-                if constexpr (H) {
-                    const char* vb = (const char*)A.vol;
-                    p00 = load_pair_h<C>(vb, voff);
-                    p10 = load_pair_h<C>(vb, voff + YS);
-                    p01 = load_pair_h<C>(vb, voff + ZS);
-                    p11 = load_pair_h<C>(vb, voff + YZ);
-                } else {
-                    const char* vb = (const char*)A.vol;
-                    p00 = load_pair_g<C>(vb, voff);
-                    p10 = load_pair_g<C>(vb, voff + YS);
-                    p01 = load_pair_g<C>(vb, voff + ZS);
-                    p11 = load_pair_g<C>(vb, voff + YZ);
-                }
-            }
+            const char* vb = (const char*)A.vol;
+            const CellPair<C> p00 = load_pair_h<C>(vb, voff), p10 = load_pair_h<C>(vb, voff + YS),
+                              p01 = load_pair_h<C>(vb, voff + ZS), p11 = load_pair_h<C>(vb, voff + YZ);
             const float bx = 1.f - ax, by = 1.f - ay, bz = 1.f - az;
             const float w00 = by * bz, w10 = ay * bz, w01 = by * az, w11 = ay * az;
             const float w000 = bx * w00, w100 = ax * w00, w010 = bx * w10, w110 = ax * w10;
@@ -1139,10 +1119,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
         }
     }
     if (A.ms.seg > 1) gather_segments<C, 256>(smem, A.ms.seg, rpb, sid, acc, nsamp);
-    if constexpr (H) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) acc[c] *= A.ihs[c];   // exact: powers of two
-    }
+    for (int c = 0; c < C; ++c) acc[c] *= A.ihs[c];   // exact: powers of two
     const bool owner = valid && sid == 0;
     const float dt = (float)g.dt;
     if (owner && A.p_out) A.p_out[iu + (size_t)g.nu * iv] = dt * acc[0];
@@ -1176,8 +1154,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
 }
 
 // ------------------------------------------ FP32 ray march, LDS-staged ----
-// The same march as k_march_f32 (same rays per wave, same segments, same
-// sample positions), but each wave gathers its taps from a private LDS copy of
+// The march of FP32 cells: rays per wave, segments and sample positions as in
+// k_march_f16, but each wave gathers its taps from a private LDS copy of
 // the cells it is about to sample instead of through the vector L1.  The
 // wave's sample range is cut into chunks of S sample indices; for each chunk
 // the wave finds the index box of the cells its rays can read (from the
@@ -1189,8 +1167,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(C <= 4
 // Each staged cell serves ~40 sample taps at paper scale, so the L1 sees a few
 // coalesced row loads per chunk instead of 8 scattered cells per sample.
 //
-// What bounds it: VALU issue first (1.16 wave-instructions per CU and clock
-// here; independent FMAs alone reach 1.48), then the LDS reads (0.56 of the
+// What bounds it: VALU issue first (1.05 wave-instructions per CU and clock at
+// 30 deg; independent FMAs alone reach 1.48), then the LDS reads (0.56 of the
 // clocks).  Hence the chunk set-up without wave reductions or divisions (the
 // box cost six reductions a chunk and the copy 19 instructions per 64 cells),
 // no clamps where the box lies inside the image, and no registers or waits in
@@ -1379,8 +1357,8 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(ma
             const int ax = lane >= 3 ? lane - 3 : lane;
             bn = ax == 0 ? A.fn1[0] : (ax == 1 ? A.fn1[1] : A.fn1[2]);
         }
-        // the chunk's samples: the same positions, weights and order as
-        // in k_march_f32; a lane reloads its cells P (the pairs at +0, +y,
+        // the chunk's samples: positions, weights and order as in
+        // k_march_f16; a lane reloads its cells P (the pairs at +0, +y,
         // +z, +y+z) only when they change
         // (fm: the sample's index relative to na, as a float; clamp: positions
         // may lie outside the support and are clamped to it -- wave-uniform)
@@ -1722,19 +1700,20 @@ __global__ void __launch_bounds__(256) k_absmax_rows(const S* __restrict__ a, si
 // prod_a max(0, 1 - |q_a - v_a|).  No global atomics, and every voxel's sum
 // is formed in a fixed order, so the result is deterministic.
 //
-// A workgroup owns a brick of 16 x 4 x 4 voxels whose long side runs along
-// the rays' dominant in-plane axis A: 16 columns of 16 voxels along A.  It
-// walks the brick's detector footprint in tiles of 8 (u) x 32 (v) pixels; per
-// tile every thread stages one ray in LDS (the sample nearest the brick centre relative
-// to the brick origin, the step per sample, slab bounds, r dt and the valid
-// sample range [0, floor(L / dt)]).  Then the 16 threads of a column split
-// the rays of the column's own footprint between them; for each ray a slab
-// test gives the samples that pass within one voxel of the column's line,
+// A workgroup owns a brick of 4 x 4 (or, see launch_backproject, 2 x 2)
+// columns of 16 voxels along the rays' dominant in-plane axis A.  It walks the
+// brick's detector footprint in tiles of 8 (u) x 32 (v) pixels; per tile every
+// thread stages one ray in LDS (the sample nearest the brick centre relative
+// to the brick origin, the step per sample, slab bounds, r dt, narrowed to the
+// valid sample range [0, floor(L / dt)]).  Then the 16 (64) threads of a column
+// split the rays of the column's own footprint between them; for each ray a
+// slab test gives the samples that pass within one voxel of the column's line,
 // and each such sample adds its weight to the two voxels of the column that
-// straddle it along A (a per-thread run of 16 accumulators in LDS).  Per ray
-// the set-up is paid once per column instead of once per voxel, and each
-// sample is visited once.  A fixed-order sum over the 16 threads of each
-// column gives the voxel values.
+// straddle it along A (two neighbouring samples at a time to three voxels,
+// where they lie less than a voxel apart), in a per-thread run of accumulators
+// in LDS.  Per ray the set-up is paid once per column instead of once per
+// voxel, and each sample is visited once.  A fixed-order sum over the threads
+// of each column gives the voxel values.
 struct BPFoot {
     // for an index-space point X: a = a0 + an.X (depth along the central
     // ray, mm), b = b0 + bn.X and c = c0 + cn.X (offsets along e_u, e_v);
@@ -1815,7 +1794,7 @@ __device__ __forceinline__ double run_voxel(double x, double hi) { return fmin(f
 // at 0 / 30 / 90 deg: 907 / 694 / 887 -> 759 / 580 / 725 us.  Tiles of 4 x 32
 // rays (six blocks) 752 / 630 / 710 us; 8 x 4 or 4 x 8 columns with 8 lanes
 // each 750-1570 us; LDS float atomics instead of the round trip 5000-5900 us
-// (they take the lanes one by one).  Two samples a turn (PAIR) halve the round
+// (they take the lanes one by one).  Two samples a turn (kPairs) halve the round
 // trips: 722 / 569 / 662 us; with the ray's weight applied in the last
 // additions, whole sample bounds as floats and positions from the column's
 // middle (error against FP64 7.4e-8 - 1.1e-7 relative, 7.9e-8 - 1.5e-7 from
@@ -1871,8 +1850,8 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     const int bid = blockIdx.x;
     const int b0[3] = {(bid % A.nbx) * A.bx, ((bid / A.nbx) % A.nby) * A.by, (bid / (A.nbx * A.nby)) * A.bz};
     const int AX = A.ax, BX = 1 - A.ax;           // column axis and the other in-plane axis
-    // a wave holds 4 columns x 16 lanes: consecutive lanes take consecutive
-    // rays of one column, so their record loads hit distinct banks
+    // a wave holds 4 columns x 16 lanes (one of 64): consecutive lanes take
+    // consecutive rays of one column, so their record loads hit distinct banks
     constexpr int LPC = 256 / (CB * CB);
     const int col = t / LPC, lane = t % LPC;        // column (lb, lz) and ray lane
     const int lb = col % CB, lz = col / CB;
@@ -1899,14 +1878,14 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
     __syncthreads();
     const int bu0 = s_box[0], bu1 = s_box[1], bv0 = s_box[2], bv1 = s_box[3];
     const double cb[3] = {b0[0] + 0.5 * (A.bx - 1), b0[1] + 0.5 * (A.by - 1), b0[2] + 0.5 * (A.bz - 1)};
-    const float flb = (float)lb, flz = (float)lz;
     const R rlb = (R)lb, rlz = (R)lz;
     // Tiles of 8 (u) x 32 (v) rays: a column's footprint is wide along u (the
     // column runs along A) and short along v, so a tall, narrow tile holds
-    // the footprints of all 16 columns at once and gives the 16 lanes of a
-    // column rays that cross it alike (the lanes of a wave then run their
-    // sample loops for similar lengths: ~0.55 of the lanes busy in the loop
-    // against ~0.3 with 16 x 16 tiles, and ~40 % fewer rounds of rays)
+    // the footprints of all columns at once and gives the lanes of a column
+    // rays that cross it alike (the lanes of a wave then run their
+    // sample loops for similar lengths: with 4 x 4 columns ~0.55 of the lanes
+    // busy in the loop against ~0.3 with 16 x 16 tiles, and ~40 % fewer rounds
+    // of rays)
     for (int tv0 = bv0; tv0 <= bv1; tv0 += TV) {
         for (int tu0 = bu0; tu0 <= bu1; tu0 += TU) {
             {   // stage one ray per thread (FP64 set-up, once per ray and brick)
@@ -2089,19 +2068,20 @@ __global__ void __launch_bounds__(256) k_backproject_columns(BPArgs A, const R* 
                         a3[256] = fma(rw, (w1 - u0) + (w2 - v0 - v2), s1);
                         a3[512] = fma(rw, v2, s2);
                     }
-                } else
-                for (R fm = (R)lo; fm <= fm1; fm += (R)1) {
-                    // (saturated differences: one instruction each in FP32)
-                    const R wbz = saturate((R)1 - fabs(fma(fm, db, qb))) *
-                                  (saturate((R)1 - fabs(fma(fm, dz, qz))) * rw);
-                    // the slab range keeps xa within (-9.01, 8.01): the clamp
-                    // only guards the LDS run
-                    const R xa = fma(fm, da, qa);
-                    const int j = (int)run_voxel(xa, (R)8);
-                    const R t1 = fract_of(xa) * wbz, t0 = wbz - t1;
-                    // the thread's own LDS run: a plain read-modify-write
-                    acc[j * 256] += t0;
-                    acc[(j + 1) * 256] += t1;
+                } else {
+                    for (R fm = (R)lo; fm <= fm1; fm += (R)1) {
+                        // (saturated differences: one instruction each in FP32)
+                        const R wbz = saturate((R)1 - fabs(fma(fm, db, qb))) *
+                                      (saturate((R)1 - fabs(fma(fm, dz, qz))) * rw);
+                        // the slab range keeps xa within (-9.01, 8.01): the clamp
+                        // only guards the LDS run
+                        const R xa = fma(fm, da, qa);
+                        const int j = (int)run_voxel(xa, (R)8);
+                        const R t1 = fract_of(xa) * wbz, t0 = wbz - t1;
+                        // the thread's own LDS run: a plain read-modify-write
+                        acc[j * 256] += t0;
+                        acc[(j + 1) * 256] += t1;
+                    }
                 }
             }
             __syncthreads();
@@ -2141,27 +2121,27 @@ __global__ void __launch_bounds__(256) k_contract(const F* __restrict__ f0,
 #pragma unroll
     for (int kk = 0; kk < KM; ++kk) m[kk] = 0.0;
     for (int k = blockIdx.z; k < g.nz; k += gridDim.z) {
-    if (i < g.nx && j < g.ny) {
-        size_t N = (size_t)g.nx * g.ny * g.nz;
-        size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
-        R gv = gpad[v];
-        if (gv != (R)0) {
-            R x[3], u[KM][3];
-            load_fields<R, S, KM, size_t>(mean, U, K, N, v * sizeof(S), w, x, u);
-            R qx = (R)i + by_spacing(x[0], g, 0);
-            R qy = (R)j + by_spacing(x[1], g, 1);
-            R qz = (R)k + by_spacing(x[2], g, 2);
-            R dT[3];
-            sample_f0<R, F, true>(f0, g.nx, g.ny, g.nz, qx, qy, qz, dT);
-            double G0 = (double)dT[0] / g.sp[0], G1 = (double)dT[1] / g.sp[1],
-                   G2 = (double)dT[2] / g.sp[2];
-            double gd = (double)gv;
-#pragma unroll
-            for (int kk = 0; kk < KM; ++kk)
-                if (kk < K)
-                    m[kk] += gd * (G0 * (double)u[kk][0] + G1 * (double)u[kk][1] + G2 * (double)u[kk][2]);
+        if (i < g.nx && j < g.ny) {
+            size_t N = (size_t)g.nx * g.ny * g.nz;
+            size_t v = (size_t)i + (size_t)g.nx * ((size_t)j + (size_t)g.ny * k);
+            R gv = gpad[v];
+            if (gv != (R)0) {
+                R x[3], u[KM][3];
+                load_fields<R, S, KM, size_t>(mean, U, K, N, v * sizeof(S), w, x, u);
+                R qx = (R)i + by_spacing(x[0], g, 0);
+                R qy = (R)j + by_spacing(x[1], g, 1);
+                R qz = (R)k + by_spacing(x[2], g, 2);
+                R dT[3];
+                sample_f0<R, F, true>(f0, g.nx, g.ny, g.nz, qx, qy, qz, dT);
+                double G0 = (double)dT[0] / g.sp[0], G1 = (double)dT[1] / g.sp[1],
+                       G2 = (double)dT[2] / g.sp[2];
+                double gd = (double)gv;
+    #pragma unroll
+                for (int kk = 0; kk < KM; ++kk)
+                    if (kk < K)
+                        m[kk] += gd * (G0 * (double)u[kk][0] + G1 * (double)u[kk][1] + G2 * (double)u[kk][2]);
+            }
         }
-    }
     }
     // threadIdx is 2-D (64 x 4): flatten for the block reduction
     __shared__ double red[4][KM];
@@ -2679,9 +2659,9 @@ static hipError_t march_f32(const PadLayout& L, int kc, const RayGeom& rg, const
     if (L.half && (L.C == 1 || ms.seg > 4)) return hipErrorInvalidValue;
     if (L.half) {
         switch (L.C) {
-        case 2: k_march_f32<2, true><<<blocks, 256, 0, s>>>(A); break;
-        case 4: k_march_f32<4, true><<<blocks, 256, 0, s>>>(A); break;
-        case 8: k_march_f32<8, true><<<blocks, 256, 0, s>>>(A); break;
+        case 2: k_march_f16<2><<<blocks, 256, 0, s>>>(A); break;
+        case 4: k_march_f16<4><<<blocks, 256, 0, s>>>(A); break;
+        case 8: k_march_f16<8><<<blocks, 256, 0, s>>>(A); break;
         default: return hipErrorInvalidValue;
         }
     } else {

@@ -31,7 +31,8 @@ constexpr int kMaxChunks = 4096;     // of the field pass
 // by HBM once the next element's J loads are in flight while this one's
 // products are formed (the 2 P registers of the sums leave four waves a SIMD,
 // too few to hide a load each by themselves): 9 fields of 3 x 6.55 M values,
-// 708 MB, 164 -> 150 us (4.7 TB/s).
+// 708 MB, 163 -> 153 us (4.6 TB/s) by events around the pass; in a kernel trace
+// of single calls, 164 us.
 template <int J>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(J <= 9 ? 4 : 1))) k_gram(const float* __restrict__ d, size_t E,
                                               double* __restrict__ partials)
