@@ -704,11 +704,9 @@ void keep_room(size_t need, int dev, hipStream_t s)
 {
     hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
     if (tls.pad.holds(need, dev) || capturing(s)) return;
-    if (hipThreadExchangeStreamCaptureMode(&m) == hipSuccess) {
-        (void)pad_room(need, dev, s);
-        (void)hipThreadExchangeStreamCaptureMode(&m);
-    }
-    (void)hipGetLastError();
+    if (hipThreadExchangeStreamCaptureMode(&m) != hipSuccess) return;
+    if (pad_room(need, dev, s) != PCR_OK) (void)hipGetLastError();   // (not needed now)
+    (void)hipThreadExchangeStreamCaptureMode(&m);
 }
 
 pcr_status current_device(int* dev)
