@@ -286,3 +286,27 @@ def test_f64_samples_do_not_move_with_the_detector(ang):
     q = L.forward_project(g, large, x).cpu().numpy()[61:67, 68:76]
     assert np.abs(q).max() > 0
     assert rel_l2(p, q) <= 1e-14
+
+
+@pytest.mark.parametrize("shift", [0.0, 0.49, -0.51, -1.0, 1.0])
+@pytest.mark.parametrize("n", [(1, 1, 1), (67, 3, 2), (130, 6, 5)])
+def test_warp_at_and_beyond_the_faces(n, shift):
+    """Voxels displaced to the image's faces, just inside, just outside and far
+    beyond, mixed within a wave: values and tangents (through the gradient's
+    contraction) are the oracle's, 1e-5 of the image and of the gradient, whose
+    terms add up without cancelling (rising image and fields)."""
+    L = _lib()
+    g = S.Grid(n, (2.0, 2.0, 2.0))
+    z = np.indices(g.shape)[::-1]
+    f_t, f = rounded(1.0 + z[0] + 2.0 * z[1] + 3.0 * z[2], torch.float32)
+    rng = np.random.default_rng(3)
+    far = rng.choice([0.0, 1.0, 40.0], size=(3,) + g.shape, p=[0.4, 0.4, 0.2]) * np.array(n)[:, None, None, None]
+    x_t, x = rounded(2.0 * (far * rng.choice([-1.0, 1.0], size=far.shape) + shift + 0.001), torch.float32)
+    got = L.warp_volume(g, f_t.to(DEV), x_t.to(DEV)).cpu().numpy()
+    assert np.linalg.norm(got - oracle.warp(g, f, x)) <= 1e-5 * np.linalg.norm(f)
+    U_t, U = rounded(np.full((1, 3) + g.shape, 0.5), torch.float32)
+    gv = torch.ones(g.shape, device=DEV)
+    model = L.DeviceModel(x_t.to(DEV), U_t.to(DEV))
+    grad = L.warp_contract(g, model, f_t.to(DEV), [0.0], gv)[0]
+    jac = oracle.warp_jacobian(g, f, x)
+    assert abs(grad - (jac * U[0]).sum()) <= 1e-5 * np.abs(jac * U[0]).sum()
